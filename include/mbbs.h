@@ -141,8 +141,11 @@ int mbbs_lattice_table(mbbs_lattice_t lat, int which, int32_t* out, size_t count
  *  MBBS_TUNE_MR_FUSED               SAP domain solver: 1 runs all MR steps of a
  *      colour in one launch, one workgroup per domain (domain-wide sums inside
  *      the workgroup); 0 uses three launches per MR step spread over the whole
- *      chip; -1 (default) picks 1 when a domain holds at most 2048 (site,
- *      column) pairs
+ *      chip; -1 (default) keeps each domain on the chip from its SAP residual to
+ *      its last step, in one launch per colour and cycle (FP64 and FP32 storage;
+ *      a large domain is shared by several workgroups; timed as MR_DSLASH, and
+ *      the group, thread, split, chunk, tile, once and hop knobs do not apply),
+ *      and else picks 1 when a domain holds at most 2048 (site, column) pairs
  *  MBBS_TUNE_NT_STORE_FP64/FP32/FP16S  1: the operator writes its output with
  *      nontemporal stores (the output is not re-read by the same launch, so it
  *      need not displace neighbour data in L2)

@@ -1,0 +1,51 @@
+// SAP domain solves kept on the chip: one launch per colour and cycle forms
+// the SAP residual of every domain, runs its nmr minimal-residual steps and
+// adds the result to psi (Sec. 2.2).  A domain and a group of columns (a
+// unit) belong to one workgroup, or to G workgroups that own a tile of the
+// domain each and exchange tile faces and partial sums through memory.
+#pragma once
+
+#include "internal.h"
+
+namespace mbbs {
+
+// Storage of eta and psi on this path, complex element of (position D of the
+// domain in domain-major order, column group cg, tile, component e, site of
+// the tile, column c of the group):
+//   ((((D ncg + cg) G + tile) 12 + e) ts + site) lg + c
+// so that a workgroup reads and writes whole runs.
+struct DomPlan {
+  int t[4];         // tile extents (each divides the SAP block extent)
+  int nt[4];        // tiles per domain and direction
+  int tstr[4];      // strides of the site index inside a tile
+  int tgs[4];       // strides of the tile index inside a domain
+  int n[4];         // entries (site, column chunk) of a tile face
+  int hoff[4][2];   // first halo entry of direction m from the tile below [0] / above [1]
+  int ts;           // sites per tile
+  int lg;           // columns per unit (divides L)
+  int C;            // columns per thread
+  int np;           // column chunks per site: lg / C
+  int T;            // threads per workgroup: ts np
+  int TS;           // cells per LDS row (256 or 512), at least T
+  int G;            // workgroups (tiles) per unit
+  int ncg;          // column groups: L / lg
+  int H;            // halo entries of a tile
+  int units;        // domains of one colour x ncg
+  int ngroups;      // workgroup groups of a launch (G > 1)
+};
+
+// Polls (about a microsecond each) after which a wait for another workgroup
+// gives up: every wait ends.  What it waited for is then missing, so its unit's
+// psi becomes NaN, which the caller's residual shows.
+constexpr int DOM_STEP_POLLS = 1 << 24;
+
+// Whether (and how) SAP with MR domain solves runs on this path for the
+// lattice, L, precision and workspace.
+bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out);
+// psi = M eta on the path of `p`: in (FP64 lexicographic, times gam if given)
+// to out.  The workspace is bound as for the other SAP kernels.
+int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p, int ncy, int nmr,
+                  const double2* in, const double2* gam, double2* out, const int* frozen, hipStream_t st,
+                  struct Profiler* prof);
+
+}  // namespace mbbs

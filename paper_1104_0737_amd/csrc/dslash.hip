@@ -5,6 +5,7 @@
 // spin-projected hops in registers.  Variants: full operator, the
 // domain-restricted (Dirichlet) operator of Sec. 2.2, the SAP residual
 // eta - A psi, and the MR domain step with its per-domain reductions.
+#include "domsolve.h"
 #include "stencil.h"
 #include "tile.h"
 
@@ -1646,6 +1647,8 @@ int sap_from(const mbbs_lattice_s* lat, const SapBuffers& b, double2* out, const
 
 int sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, int nmr, const double2* in,
               const double2* gam, double2* out, const int* frozen, hipStream_t st, Profiler* prof) {
+  DomPlan dp;
+  if (dom_plan(lat, b, &dp)) return dom_sap_apply(lat, b, dp, ncy, nmr, in, gam, out, frozen, st, prof);
   if (prof) prof->begin(MBBS_K_CONVERT);
   MBBS_TRY(sap_to(lat, b, in, gam, b.eta, b.eta_s, frozen, st));
   if (prof) prof->end();

@@ -114,6 +114,11 @@ struct mbbs_lattice_s {
   double2* U64dm = nullptr;   // domain-major links
   float2* U32dm = nullptr;
   __half2* U16dm = nullptr;
+  // links in the domain-plane layout per precision: 16-byte vector i of the
+  // link in direction mu at local site loc of the domain at position D sits at
+  // ((D 4 + mu) NL + i) Vb + loc, NL = 9 / 5 vectors per link (FP64 / FP32, the
+  // latter padded): lanes on neighbouring sites read neighbouring vectors
+  void* Udp[2] = {nullptr, nullptr};
   // launch tuning (set through mbbs_lattice_tune): columns per column group
   // of the stencil kernels per precision (0: all columns in one group) and
   // the target number of threads per block

@@ -36,6 +36,25 @@ __global__ void k_links(GeomK k, const double2* __restrict__ U, float2* __restri
   }
 }
 
+// The domain-plane layout of the links (internal.h), from the domain-major ones.
+__global__ void k_link_planes(GeomK k, const double2* __restrict__ U64dm, double2* __restrict__ P64p,
+                              float4* __restrict__ P32p) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // domain-major position
+  if (i >= k.g.V) return;
+  const int Vb = k.g.Vb, D = i / Vb, loc = i - D * Vb;
+  for (int mu = 0; mu < 4; ++mu) {
+    float2 f[10];
+    f[9] = make_float2(0, 0);
+    for (int e = 0; e < 9; ++e) {
+      const double2 v = U64dm[(size_t)i * 36 + mu * 9 + e];
+      P64p[((size_t)(D * 4 + mu) * 9 + e) * Vb + loc] = v;
+      f[e] = make_float2((float)v.x, (float)v.y);
+    }
+    for (int q = 0; q < 5; ++q)
+      P32p[((size_t)(D * 4 + mu) * 5 + q) * Vb + loc] = make_float4(f[2 * q].x, f[2 * q].y, f[2 * q + 1].x, f[2 * q + 1].y);
+  }
+}
+
 // All per-site tables, from the kernels' own index functions.
 __global__ void k_tables(GeomK k, int which, int32_t* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -221,6 +240,16 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
   }
   hipLaunchKernelGGL(k_links, dim3(ceil_div(V, 256)), dim3(256), 0, st, lat->gk, (const double2*)lat->U64, lat->U32,
                      lat->U16, lat->U64dm, lat->U32dm, lat->U16dm);
+  // without room for the domain-plane links the kernels that read the
+  // domain-major ones serve instead
+  const size_t nl = (size_t)V * 4 * 16;
+  if (hipMalloc(&lat->Udp[P64], nl * 9) == hipSuccess && hipMalloc(&lat->Udp[P32], nl * 5) == hipSuccess) {
+    hipLaunchKernelGGL(k_link_planes, dim3(ceil_div(V, 256)), dim3(256), 0, st, lat->gk, (const double2*)lat->U64dm,
+                       (double2*)lat->Udp[P64], (float4*)lat->Udp[P32]);
+  } else {
+    (void)hipGetLastError();
+    for (void*& u : lat->Udp) { (void)hipFree(u); u = nullptr; }
+  }
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     set_error("link conversion failed");
     return fail(MBBS_EHIP);
@@ -282,6 +311,7 @@ extern "C" int mbbs_lattice_destroy(mbbs_lattice_t lat) {
   (void)hipFree(lat->U64dm);
   (void)hipFree(lat->U32dm);
   (void)hipFree(lat->U16dm);
+  for (void* u : lat->Udp) (void)hipFree(u);
   (void)hipFree(lat->hp_loc);
   (void)hipFree(lat->hp_off);
   (void)hipFree(lat->cl64);
