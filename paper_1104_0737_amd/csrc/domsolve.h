@@ -48,4 +48,12 @@ int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
                   const double2* in, const double2* gam, double2* out, const int* frozen, hipStream_t st,
                   struct Profiler* prof);
 
+// FP64 lexicographic block (times gam if given) <-> the storage of `p` in FP64
+// or FP32.  order: the local sites in storage order (null: as the tiles of `p`
+// have them).  dom_to also clears nclear words.
+int dom_to(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const double2* in,
+           const double2* gam, void* out, unsigned* clear, int nclear, const int* frozen, hipStream_t st);
+int dom_from(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const void* in,
+             double2* out, const int* frozen, hipStream_t st);
+
 }  // namespace mbbs

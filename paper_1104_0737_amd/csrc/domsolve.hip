@@ -29,15 +29,12 @@
 #include <algorithm>
 
 #include "domsolve.h"
-#include "stencil.h"
+#include "planes.h"
 
 namespace mbbs {
 
 namespace {
 
-// C adjacent columns of one complex component.
-template <typename R, int C> struct ColVec { typedef R T __attribute__((ext_vector_type(2 * C))); };
-typedef unsigned u4 __attribute__((ext_vector_type(4)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 
 // Cells of a component row in LDS: TS of the tile and one that stays zero; 12
@@ -162,21 +159,6 @@ __device__ __forceinline__ void project_rt(int m, int fwd, const V (&p)[12], V (
     case 6: project<3, 0, R, C>(p, h); break;
     default: project<3, 1, R, C>(p, h); break;
   }
-}
-
-// Vectors of 16 bytes that hold a link in the domain-plane layout (internal.h).
-template <int PR> constexpr int link_vecs() { return PR == P64 ? 9 : 5; }
-// The link in direction MU whose first vector (of direction 0) is vector li.
-template <int PR, int MU>
-__device__ __forceinline__ void plane_link(const u4* __restrict__ U, unsigned li, int Vb, typename RawT<PR>::T* lk) {
-  constexpr int NL = link_vecs<PR>(), W = 9 * RawT<PR>::per * (int)sizeof(typename RawT<PR>::T) / 4;
-  unsigned w[4 * NL];
-#pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const u4 v = (U + (size_t)(MU * NL + i) * Vb)[li];
-    w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
-  }
-  __builtin_memcpy(lk, w, 4 * W);
 }
 
 // One hop: the neighbour's components from LDS cell a (rows as in DomLds; a
@@ -775,17 +757,21 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
 // ------------------------------------------------------------- conversions
 // Blocks of SB consecutive sites of the (domain, tile, site) order.
 struct DomSite { int lex, sys; size_t tile; int site; };
-__device__ __forceinline__ DomSite dom_site(const GeomK& k, const DomPlan& P, int q) {
+__device__ __forceinline__ DomSite dom_site(const GeomK& k, const DomPlan& P, const int* __restrict__ order, int q) {
   DomSite d;
   const int tile_g = q / P.ts;            // tile over the lattice
   d.site = q - tile_g * P.ts;
   const int D = tile_g / P.G, tile = tile_g - D * P.G;
   int a = d.site, b = tile, loc = 0;
+  if (order) {
+    loc = order[d.site];
+  } else {
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int ra = a / P.t[m], rb = b / P.nt[m];
-    loc += ((b - rb * P.nt[m]) * P.t[m] + (a - ra * P.t[m])) * k.lstride[m];
-    a = ra; b = rb;
+    for (int m = 0; m < 4; ++m) {
+      const int ra = a / P.t[m], rb = b / P.nt[m];
+      loc += ((b - rb * P.nt[m]) * P.t[m] + (a - ra * P.t[m])) * k.lstride[m];
+      a = ra; b = rb;
+    }
   }
   const SiteCtx c = site_ctx<DM>(k, D * k.g.Vb + loc);
   d.lex = lex_of(k, c);
@@ -802,14 +788,14 @@ template <int PR>
 __global__ void __launch_bounds__(256) k_to_dom(GeomK k, DomPlan P, int L, int SB, const double2* __restrict__ in,
                                                 const double2* __restrict__ gam, typename Store<PR>::Elem* __restrict__ out,
                                                 unsigned* __restrict__ clear, int nclear,
-                                                const int* __restrict__ frozen) {
+                                                const int* __restrict__ order, const int* __restrict__ frozen) {
   using R = typename Store<PR>::Real;
   extern __shared__ double2 gsh[];
   __shared__ DomSite ds[16];
   const int tid = threadIdx.x, nthr = blockDim.x;
   for (int i = blockIdx.x * nthr + tid; i < nclear; i += gridDim.x * nthr) clear[i] = 0;
   const int q0 = blockIdx.x * SB;
-  if (tid < SB) ds[tid] = dom_site(k, P, q0 + tid);
+  if (tid < SB) ds[tid] = dom_site(k, P, order, q0 + tid);
   __syncthreads();
   // SB divides the domain volume: one system per block
   const int sys = ds[0].sys;
@@ -865,13 +851,14 @@ __global__ void __launch_bounds__(256) k_to_dom(GeomK k, DomPlan P, int L, int S
 
 template <typename R>
 __global__ void __launch_bounds__(256) k_from_dom(GeomK k, DomPlan P, int L, int SB, const cplx<R>* __restrict__ in,
-                                                  double2* __restrict__ out, const int* __restrict__ frozen) {
+                                                  double2* __restrict__ out, const int* __restrict__ order,
+                                                  const int* __restrict__ frozen) {
   extern __shared__ double2 gsh[];
   __shared__ DomSite ds[16];
   cplx<R>* ish = (cplx<R>*)gsh;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int q0 = blockIdx.x * SB;
-  if (tid < SB) ds[tid] = dom_site(k, P, q0 + tid);
+  if (tid < SB) ds[tid] = dom_site(k, P, order, q0 + tid);
   __syncthreads();
   if (sys_frozen(k, frozen, ds[0].sys)) return;
   const int lg = P.lg, row = 12 * L;
@@ -1046,25 +1033,43 @@ bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
   return true;
 }
 
+int dom_to(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const double2* in,
+           const double2* gam, void* out, unsigned* clear, int nclear, const int* frozen, hipStream_t st) {
+  const Geom& g = lat->g;
+  const int SB = conv_sites(g.Vb, L), nb = g.V / SB, thr = (SB * L + 63) / 64 * 64;
+  const size_t shm = ((size_t)SB * 12 * L + (gam ? (size_t)L * L : 0)) * sizeof(double2);
+  if (prec == P64)
+    hipLaunchKernelGGL(k_to_dom<P64>, dim3(nb), dim3(thr), shm, st, lat->gk, p, L, SB, in, gam, (double2*)out, clear,
+                       nclear, order, frozen);
+  else
+    hipLaunchKernelGGL(k_to_dom<P32>, dim3(nb), dim3(thr), shm, st, lat->gk, p, L, SB, in, gam, (float2*)out, clear,
+                       nclear, order, frozen);
+  MBBS_HIP(hipGetLastError());
+  return MBBS_OK;
+}
+int dom_from(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const void* in,
+             double2* out, const int* frozen, hipStream_t st) {
+  const Geom& g = lat->g;
+  const int SB = conv_sites(g.Vb, L), nb = g.V / SB, thr = (SB * L + 63) / 64 * 64;
+  const size_t rows = (size_t)SB * 12 * L;
+  if (prec == P64)
+    hipLaunchKernelGGL(k_from_dom<double>, dim3(nb), dim3(thr), rows * 16, st, lat->gk, p, L, SB,
+                       (const cplx<double>*)in, out, order, frozen);
+  else
+    hipLaunchKernelGGL(k_from_dom<float>, dim3(nb), dim3(thr), rows * 8, st, lat->gk, p, L, SB, (const cplx<float>*)in,
+                       out, order, frozen);
+  MBBS_HIP(hipGetLastError());
+  return MBBS_OK;
+}
+
 int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p, int ncy, int nmr,
                   const double2* in, const double2* gam, double2* out, const int* frozen, hipStream_t st,
                   Profiler* prof) {
-  const Geom& g = lat->g;
-  const int L = b.L, SB = conv_sites(g.Vb, L), nb = g.V / SB;
-  const int thr = (SB * L + 63) / 64 * 64;
   const int nlaunch = 2 * ncy;
   const size_t nclear = p.G > 1 ? sync_ints(p) : 0;
-  const size_t rows = (size_t)SB * 12 * L * sizeof(double2);
-  const size_t shm = rows + (gam ? (size_t)L * L * sizeof(double2) : 0);
   unsigned* clear = (unsigned*)b.r;
   if (prof) prof->begin(MBBS_K_CONVERT);
-  if (b.prec == P64)
-    hipLaunchKernelGGL(k_to_dom<P64>, dim3(nb), dim3(thr), shm, st, lat->gk, p, L, SB, in, gam, (double2*)b.eta, clear,
-                       (int)nclear, frozen);
-  else
-    hipLaunchKernelGGL(k_to_dom<P32>, dim3(nb), dim3(thr), shm, st, lat->gk, p, L, SB, in, gam, (float2*)b.eta, clear,
-                       (int)nclear, frozen);
-  MBBS_HIP(hipGetLastError());
+  MBBS_TRY(dom_to(lat, b.prec, b.L, p, nullptr, in, gam, b.eta, clear, (int)nclear, frozen, st));
   if (prof) prof->end();
   DomSync sy{};
   sy.step_polls = DOM_STEP_POLLS;
@@ -1088,13 +1093,7 @@ int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
     if (prof) prof->end();
   }
   if (prof) prof->begin(MBBS_K_CONVERT);
-  if (b.prec == P64)
-    hipLaunchKernelGGL(k_from_dom<double>, dim3(nb), dim3(thr), rows, st, lat->gk, p, L, SB, (const cplx<double>*)b.psi,
-                       out, frozen);
-  else
-    hipLaunchKernelGGL(k_from_dom<float>, dim3(nb), dim3(thr), rows / 2, st, lat->gk, p, L, SB,
-                       (const cplx<float>*)b.psi, out, frozen);
-  MBBS_HIP(hipGetLastError());
+  MBBS_TRY(dom_from(lat, b.prec, b.L, p, nullptr, b.psi, out, frozen, st));
   if (prof) prof->end();
   return MBBS_OK;
 }

@@ -1649,6 +1649,11 @@ int sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, int nmr, 
               const double2* gam, double2* out, const int* frozen, hipStream_t st, Profiler* prof) {
   DomPlan dp;
   if (dom_plan(lat, b, &dp)) return dom_sap_apply(lat, b, dp, ncy, nmr, in, gam, out, frozen, st, prof);
+  if (b.ssor) {
+    bool done = false;
+    const int rc = ssor_sap_apply(lat, b, ncy, in, gam, out, frozen, st, prof, &done);
+    if (rc != MBBS_OK || done) return rc;
+  }
   if (prof) prof->begin(MBBS_K_CONVERT);
   MBBS_TRY(sap_to(lat, b, in, gam, b.eta, b.eta_s, frozen, st));
   if (prof) prof->end();

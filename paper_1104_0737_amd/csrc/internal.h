@@ -119,6 +119,8 @@ struct mbbs_lattice_s {
   // ((D 4 + mu) NL + i) Vb + loc, NL = 9 / 5 vectors per link (FP64 / FP32, the
   // latter padded): lanes on neighbouring sites read neighbouring vectors
   void* Udp[2] = {nullptr, nullptr};
+  // the same with the local sites in wavefront order (hp_loc) instead
+  void* Uhp[2] = {nullptr, nullptr};
   // launch tuning (set through mbbs_lattice_tune): columns per column group
   // of the stencil kernels per precision (0: all columns in one group) and
   // the target number of threads per block
@@ -145,6 +147,13 @@ struct mbbs_lattice_s {
   double csw = 0;
   int* hp_loc = nullptr;
   int* hp_off = nullptr;
+  // per entry of hp_loc four 16-bit places (in hp_loc's order) of its forward
+  // [0..Vb-1] and backward [Vb..2Vb-1] in-domain neighbours, 0xffff if none; and
+  // per direction both neighbours' places (low half: forward), a hop that
+  // leaves wrapped into the neighbouring domain (absent where a place needs
+  // more than 16 bits)
+  uint2* hp_nb = nullptr;
+  uint4* hp_wrap = nullptr;
   int nh = 0;          // number of hyperplanes, sum_mu (b_mu - 1) + 1
   int hp_max = 0;      // sites in the largest hyperplane
 };
@@ -202,6 +211,9 @@ int sap_from(const mbbs_lattice_s* lat, const SapBuffers& b, double2* out, const
 // formed inside the first sweep.  r, w and x2 are overwritten.
 int ssor_colour(const mbbs_lattice_s* lat, const SapBuffers& b, int colour, bool assign, int rmode,
                 const int* frozen, hipStream_t st);
+// SAP with SSOR domain solves through LDS, where that serves (*done), else nothing.
+int ssor_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, const double2* in, const double2* gam,
+                   double2* out, const int* frozen, hipStream_t st, struct Profiler* prof, bool* done);
 // out = B in on every domain (both colours), FP64 lexicographic blocks.
 int ssor_blocked_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const double2* in, double2* out,
                        hipStream_t st);

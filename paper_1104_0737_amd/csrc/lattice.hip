@@ -36,17 +36,19 @@ __global__ void k_links(GeomK k, const double2* __restrict__ U, float2* __restri
   }
 }
 
-// The domain-plane layout of the links (internal.h), from the domain-major ones.
-__global__ void k_link_planes(GeomK k, const double2* __restrict__ U64dm, double2* __restrict__ P64p,
+// A plane-wise layout of the links (internal.h), from the domain-major ones;
+// order: place -> local site (null: the same).
+__global__ void k_link_planes(GeomK k, const int* __restrict__ order, const double2* __restrict__ U64dm, double2* __restrict__ P64p,
                               float4* __restrict__ P32p) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // domain-major position
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= k.g.V) return;
   const int Vb = k.g.Vb, D = i / Vb, loc = i - D * Vb;
+  const size_t src = (size_t)D * Vb + (order ? order[loc] : loc);
   for (int mu = 0; mu < 4; ++mu) {
     float2 f[10];
     f[9] = make_float2(0, 0);
     for (int e = 0; e < 9; ++e) {
-      const double2 v = U64dm[(size_t)i * 36 + mu * 9 + e];
+      const double2 v = U64dm[src * 36 + mu * 9 + e];
       P64p[((size_t)(D * 4 + mu) * 9 + e) * Vb + loc] = v;
       f[e] = make_float2((float)v.x, (float)v.y);
     }
@@ -171,6 +173,19 @@ using namespace mbbs;
 // systems are stacked along t (system s owns t in [s Lt, (s + 1) Lt), its t
 // hops wrap inside that range) and every kernel of the handle treats them
 // as independent systems with hopping parameters kappa[s].
+// One plane-wise copy of the links in FP64 and FP32.  Without room for it the
+// kernels that read the domain-major links serve instead.
+static void link_planes(mbbs_lattice_s* lat, const int* order, void* (&U)[2], hipStream_t st) {
+  const size_t nl = (size_t)lat->g.V * 4 * 16;
+  if (hipMalloc(&U[P64], nl * 9) == hipSuccess && hipMalloc(&U[P32], nl * 5) == hipSuccess) {
+    hipLaunchKernelGGL(k_link_planes, dim3(ceil_div(lat->g.V, 256)), dim3(256), 0, st, lat->gk, order,
+                       (const double2*)lat->U64dm, (double2*)U[P64], (float4*)U[P32]);
+  } else {
+    (void)hipGetLastError();
+    for (void*& u : U) { (void)hipFree(u); u = nullptr; }
+  }
+}
+
 static int lattice_create(const int dims[4], const int block[4], int nsys, const double* const* U_dev,
                           const double* kappa, const double phase[8], void* stream, mbbs_lattice_t* out) {
   MBBS_CHECK(dims && block && U_dev && kappa && phase && out, "null argument");
@@ -240,16 +255,7 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
   }
   hipLaunchKernelGGL(k_links, dim3(ceil_div(V, 256)), dim3(256), 0, st, lat->gk, (const double2*)lat->U64, lat->U32,
                      lat->U16, lat->U64dm, lat->U32dm, lat->U16dm);
-  // without room for the domain-plane links the kernels that read the
-  // domain-major ones serve instead
-  const size_t nl = (size_t)V * 4 * 16;
-  if (hipMalloc(&lat->Udp[P64], nl * 9) == hipSuccess && hipMalloc(&lat->Udp[P32], nl * 5) == hipSuccess) {
-    hipLaunchKernelGGL(k_link_planes, dim3(ceil_div(V, 256)), dim3(256), 0, st, lat->gk, (const double2*)lat->U64dm,
-                       (double2*)lat->Udp[P64], (float4*)lat->Udp[P32]);
-  } else {
-    (void)hipGetLastError();
-    for (void*& u : lat->Udp) { (void)hipFree(u); u = nullptr; }
-  }
+  link_planes(lat, nullptr, lat->Udp, st);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     set_error("link conversion failed");
     return fail(MBBS_EHIP);
@@ -280,6 +286,45 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
         hipMemcpy(lat->hp_off, off.data(), (nh + 1) * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
       set_error("wavefront table copy failed");
       return fail(MBBS_EHIP);
+    }
+    if (g.Vb < 65535) {
+      std::vector<int> place(g.Vb);
+      for (int p = 0; p < g.Vb; ++p) place[loc[p]] = p;
+      std::vector<uint2> nb(2 * (size_t)g.Vb);
+      std::vector<uint4> wrap(g.Vb);
+      for (int p = 0; p < g.Vb; ++p)
+        for (int f = 0; f < 2; ++f) {
+          unsigned e[4], w[4];
+          int q = loc[p], stride = 1;
+          for (int m = 0; m < 4; ++m) {
+            const int l = q % g.b[m];
+            q /= g.b[m];
+            const bool in = f == 0 ? l + 1 < g.b[m] : l > 0;
+            e[m] = in ? (unsigned)place[loc[p] + (f == 0 ? stride : -stride)] : 0xffffu;
+            const int lw = f == 0 ? (in ? l + 1 : 0) : (in ? l - 1 : g.b[m] - 1);
+            w[m] = (unsigned)place[loc[p] + (lw - l) * stride] << (16 * f);
+            stride *= g.b[m];
+          }
+          uint4& o = wrap[p];
+          if (f == 0) o = make_uint4(w[0], w[1], w[2], w[3]);
+          else o = make_uint4(o.x | w[0], o.y | w[1], o.z | w[2], o.w | w[3]);
+          nb[(size_t)f * g.Vb + p] = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
+        }
+      if (hipMalloc(&lat->hp_nb, nb.size() * sizeof(uint2)) != hipSuccess ||
+          hipMalloc(&lat->hp_wrap, g.Vb * sizeof(uint4)) != hipSuccess) {
+        set_error("out of device memory for the wavefront tables");
+        return fail(MBBS_ENOMEM);
+      }
+      if (hipMemcpy(lat->hp_nb, nb.data(), nb.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess ||
+          hipMemcpy(lat->hp_wrap, wrap.data(), g.Vb * sizeof(uint4), hipMemcpyHostToDevice) != hipSuccess) {
+        set_error("wavefront table copy failed");
+        return fail(MBBS_EHIP);
+      }
+      link_planes(lat, lat->hp_loc, lat->Uhp, st);
+      if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+        set_error("link conversion failed");
+        return fail(MBBS_EHIP);
+      }
     }
   }
   *out = lat;
@@ -312,6 +357,9 @@ extern "C" int mbbs_lattice_destroy(mbbs_lattice_t lat) {
   (void)hipFree(lat->U32dm);
   (void)hipFree(lat->U16dm);
   for (void* u : lat->Udp) (void)hipFree(u);
+  for (void* u : lat->Uhp) (void)hipFree(u);
+  (void)hipFree(lat->hp_nb);
+  (void)hipFree(lat->hp_wrap);
   (void)hipFree(lat->hp_loc);
   (void)hipFree(lat->hp_off);
   (void)hipFree(lat->cl64);
