@@ -7,7 +7,7 @@
 // last update: eta passes once, psi once per step (through L2), and the FP32
 // vector units and the latencies of the exchange, not HBM, bound the launch.
 // Measured, SAP with 4 cycles of 4 steps, 8^4 domains, 12 columns: FP32 on
-// 32^3 x 64 sites 79.7 -> 40.9 ms, FP64 on 16^3 x 32 10.4 -> 6.15 ms; 4^4
+// 32^3 x 64 sites 79.7 -> 40.6 ms, FP64 on 16^3 x 32 10.4 -> 5.98 ms; 4^4
 // domains, 8^4 sites, 4 columns (2 cycles): FP32 0.52 -> 0.17 ms.
 //
 // A domain that fits one workgroup (256 threads, one site and C columns each)
@@ -22,6 +22,10 @@
 // workgroups start, so only resident workgroups wait for each other: at most
 // G - 1 workgroups of a launch can wait for members that have not started.
 // Every wait is bounded (DOM_STEP_POLLS).
+// Faces that carry their own validity (a mark that the reader puts back, no
+// flag) took 6 % off small lattices and added 3 to 8 % to large ones, where the
+// exchange's bandwidth counts; two workgroups of 256 threads per CU instead of
+// one of 512 added 10 %.
 //
 // FP16 storage of r is left to the launches of their own: rounding r and w to
 // halves costs this kernel more than it saves (3.96 -> 3.27 ms where FP32 gains
@@ -292,7 +296,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
         __hip_atomic_store(&A->sy.counters_next[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    __syncthreads();
+    lds_barrier();
     gid = uniform(ish[0]);
     mem = uniform(ish[1]);
   }
@@ -349,7 +353,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
   } else {
     ++tag;
     if (tid == 0) next_unit();
-    __syncthreads();
+    lds_barrier();
     unit = uniform(ish[3]);
   }
 
@@ -438,7 +442,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
     // all of the workgroup's published faces are in memory: tell the readers
     auto published = [&](unsigned tg) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
+      lds_barrier();
       if (tid == 0) st_word(&flags[tl], (unsigned long long)tg << 32);
     };
 
@@ -513,11 +517,11 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
         };
         R token = 0;
         stage(0);
-        __syncthreads();
+        lds_barrier();
         if (act) dom_hops<PR, C, TS, 0, R>(sh, (const u4*)A->U, li, A->Vb, cell, back, acc, token);
-        __syncthreads();
+        lds_barrier();
         stage(2);
-        __syncthreads();
+        lds_barrier();
         if (act) {
           dom_hops<PR, C, TS, 2, R>(sh, (const u4*)A->U, li, A->Vb, cell, back, acc, token);
           if (A->clov) dom_clover<C, R>(A, Dm * A->Vb + loc, acc);
@@ -543,7 +547,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
 #pragma unroll
         for (int q = 0; q < C; ++q) { r[e][2 * q] = acc[e / 3][e % 3][q].re; r[e][2 * q + 1] = acc[e / 3][e % 3][q].im; }
       if (fresh) {
-        __syncthreads();   // psi's rows are read until here
+        lds_barrier();   // psi's rows are read until here
         for (int e = tid; e < 6; e += nthr) sh[e * D::ST + D::ZERO] = V(0);
       }
       if (act) {
@@ -554,7 +558,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
     };
     put_r(true);
     if (A->P.G > 1) published(tag);
-    __syncthreads();
+    lds_barrier();
 
     // ---- the MR steps
     for (int step = 0; step < A->nmr; ++step) {
@@ -579,7 +583,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
             if (!wait_word(&flags[tl + (f ? A->P.tgs[m] : -A->P.tgs[m])], ftag, lost ? 1 : A->sy.step_polls, low)) ish[2] = 3;
           }
         }
-        __syncthreads();
+        lds_barrier();
         asm volatile("" ::: "memory");
         if (tid < A->P.H) {
           // entry tid of the halo: its direction and side
@@ -602,7 +606,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
             for (int e = 0; e < NF; ++e) sh[D::HROW + e * D::ST + tid] = h[e];
           }
         }
-        __syncthreads();
+        lds_barrier();
       }
       auto cell = [&](int m, int f) -> int {
         const unsigned c = (code >> (4 * m + 2 * f)) & 3;
@@ -648,7 +652,15 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           const double x = row_sum(sums[q][m], A->P.np);
           if ((tid & 15) < A->P.np) red[(m * 16 + (tid & 15) * C + q) * NROW + (tid >> 4)] = x;
         }
-      __syncthreads();
+      lds_barrier();
+      const bool assign = step == 0 && A->mode != 2;
+      // psi, on its way while the sums are (after them: FP64 6.05 instead of 5.98
+      // ms, FP32 41.1 instead of 40.6 at the sizes above)
+      V ps[12];
+      if (act && !assign) {
+#pragma unroll
+        for (int e = 0; e < 12; ++e) ps[e] = ((V*)A->psi + own + e * A->P.T)[me];
+      }
       const bool last = step + 1 == A->nmr;
       const int lg = A->P.lg, nrow = nthr >> 4;
       // thread (column, 16 lanes): total of the tile; then of the domain
@@ -697,7 +709,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
         }
       }
       if (A->P.G > 1 && last && tid == 0) next_unit();
-      __syncthreads();
+      lds_barrier();
       if (A->P.G > 1) lost = lost || uniform(ish[2]) == 3;
       cplx<R> om[C];
 #pragma unroll
@@ -707,7 +719,6 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
       }
       if (!last) ++tag;
       // psi += omega r; r -= omega w (r first: its faces travel meanwhile)
-      const bool assign = step == 0 && A->mode != 2;
       {
         cplx<R> x[4][3][C];   // r before the update
 #pragma unroll
@@ -720,12 +731,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           }
         }
         if (!last) put_r(false);
-        V ps[12];
         if (act) {
-          if (!assign) {
-#pragma unroll
-            for (int e = 0; e < 12; ++e) ps[e] = ((V*)A->psi + own + e * A->P.T)[me];
-          }
 #pragma unroll
           for (int e = 0; e < 12; ++e)
 #pragma unroll
@@ -745,12 +751,12 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           for (int e = 0; e < 12; ++e) ((V*)A->psi + own + e * A->P.T)[me] = ps[e];
         }
       }
-      if (last || A->P.G == 1) __syncthreads();
+      if (last || A->P.G == 1) lds_barrier();
     }
     if (A->P.G == 1) break;
     unit = uniform(ish[3]);
     if (lost) unit = -1;
-    __syncthreads();
+    lds_barrier();
   }
 }
 
