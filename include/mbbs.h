@@ -120,7 +120,11 @@ enum {
 int mbbs_lattice_table_size(mbbs_lattice_t lat, int which, size_t* count);
 int mbbs_lattice_table(mbbs_lattice_t lat, int which, int32_t* out, size_t count);
 
-/* Launch tuning of the stencil kernels (what an autotuner varies).  The
+/* Launch tuning of the stencil kernels (what an autotuner varies).  Until a
+ * GROUP, BLOCK_THREADS, SPLIT, HOP_PAIR, NT_STORE, CHUNK, TILE, TILE_COLS, LDS_PAD
+ * or PERSIST knob of a precision is set, that precision's operator on a whole
+ * lattice chooses tiles, columns per thread and block size by the lattice's
+ * size; setting one puts the others at the defaults below.  The
  * operator's output is bit-identical under the group, thread and LDS knobs;
  * the split knob changes the order in which the eight hops are summed, and
  * the SAP domain sums follow the block shape, so those change rounding only

@@ -988,8 +988,7 @@ bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
   if (((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.psi) & 15) return false;
   // links are addressed by 32-bit byte offsets
   if ((size_t)g.V * 4 * (prec == P64 ? 9 : 5) * 16 >= (1ull << 32)) return false;
-  int ncu = 0;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, lat->device) != hipSuccess) return false;
+  const int ncu = lat->ncu;
   // Two columns per thread in FP32 arithmetic (a link serves both) and the
   // largest tiles, unless a launch would then leave CUs without a workgroup.
   const int cmax = prec == P64 || L % 2 ? 1 : 2;

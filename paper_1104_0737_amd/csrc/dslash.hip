@@ -908,17 +908,58 @@ static int sites_per_block(int nchunk, int vdiv, int target = 256) {
 struct Plan {
   int C, gw, nchunk, ngroups, S, bpt, nblocks;
 };
-static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites) {
+static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites, int C, int threads) {
   Plan p;
-  p.C = pick_chunk(lat, L, prec);
+  p.C = C;
   p.gw = lat->group_cols[prec];
   if (p.gw <= 0 || p.gw % p.C || L % p.gw) p.gw = L;
   p.nchunk = p.gw / p.C;
   p.ngroups = L / p.gw;
-  p.S = sites_per_block(p.nchunk, lat->g.Vb, lat->block_threads[prec]);
+  p.S = sites_per_block(p.nchunk, lat->g.Vb, threads);
   p.bpt = lat->g.Vb / p.S;
   p.nblocks = (nsites / lat->g.Vb) * p.ngroups * p.bpt;
   return p;
+}
+static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites) {
+  return make_plan(lat, L, prec, nsites, pick_chunk(lat, L, prec), lat->block_threads[prec]);
+}
+
+// How the operator runs: LDS-tiled or one thread per site and C columns.
+struct OpSetting { int tile, C, threads, pair, nt; };
+
+// The caller's settings, or, on the whole lattice and if none was chosen for
+// the precision, by size (n = sites of a system x L; former -> now in us on 256
+// CUs).  What can change bits (FP16S, and the clover term's products, by columns
+// per thread) looks at one system: a batch runs its systems as they run alone.
+//  - Tiles from n = 200000 on (FP64: from 65536 sites on), where the neighbours'
+//    traffic counts: FP64 12^4 L = 12 46.4 -> 41.6, 16^4 L = 1 33.0 -> 25.8,
+//    16^3 x 32 L = 12 304 -> 246, 32^3 x 64 L = 12 4672 -> 3958; FP32 12^4 L = 12
+//    29.5 -> 25.1, 16^3 x 32 L = 12 177 -> 117, 32^3 x 64 L = 12 2857 -> 1912.  Below,
+//    staging is a latency more: FP64 8^4 L = 4 9.3 -> 16.  FP64 stores bypass the
+//    caches from 4 columns on (32^3 x 64 L = 12 4055 -> 3930; L = 1 no gain).
+//    FP16S: level with one column per thread, or behind.
+//  - Else one column per thread in small lattices, for more threads (FP32 8^4
+//    L = 4 14.3 -> 7.4, FP16S 14.5 -> 8.2), and from n = 200000 on with both hops of
+//    a direction in flight (FP32 24^3 x 48 L = 4 497 -> 349, L = 5 468 -> 431, FP64
+//    L = 3 581 -> 511).  Between, two columns share a link (FP32 12^4 L = 8 18.5,
+//    19.7 with one).  FP16S: one column also where four make whole 16-byte rows
+//    (16^3 x 32 L = 12 86 -> 82, L = 4 54 -> 38, but L = 6 71 -> 85), no pairs (L = 3
+//    50 -> 57).
+//  - Blocks of 64 threads where 256 leave half the CUs without one (FP64 8^4 L = 1
+//    16.1 -> 8.9, L = 4 9.3 -> 7.9), or some CUs with two and some with one (FP16S
+//    clover 12^4 L = 5 18.9 -> 17.7); with more columns a block of 64 has few
+//    sites and re-reads more (8^3 x 16 L = 12 14.9 -> 17.1: 256 stays).
+static OpSetting op_setting(const mbbs_lattice_s* lat, int L, int prec, bool whole_op) {
+  OpSetting o{-1, pick_chunk(lat, L, prec), lat->block_threads[prec], lat->hop_pair[prec], lat->nt_store[prec]};
+  if (!whole_op || lat->op_set[prec]) return o;
+  const size_t V = (size_t)lat->g.V / lat->nsys, n = V * L, ncu = lat->ncu;
+  o.tile = prec != P16 && (n >= 200000 || (prec == P64 && V >= 65536));
+  o.nt = o.tile && prec == P64 && L >= 4;
+  o.pair = prec != P16 && n >= 200000;
+  if (prec == P16 ? (L % 4 == 0 || n <= 256 * ncu) : (n <= 100000 || o.pair)) o.C = 1;
+  const size_t nb = ((size_t)lat->g.V * L / o.C + 255) / 256;
+  if (2 * nb <= ncu || (nb > ncu && nb <= 2 * ncu && L <= 8)) o.threads = 64;
+  return o;
 }
 
 // Sites per block of a split-wave launch: S divides the block volume, S*L is
@@ -990,8 +1031,8 @@ static int dslash_split_launch(const mbbs_lattice_s* lat, int L, int order, bool
 template <int PIN, int POUT, int PL, int C>
 static int dslash_dispatch_order(const mbbs_lattice_s* lat, int L, int order, bool blocked,
                                  const void* in, const float* in_s, void* out, float* out_s,
-                                 int s0, int n, const int* frozen, hipStream_t st) {
-  const Plan pl = make_plan(lat, L, PL, n);
+                                 int s0, int n, const OpSetting& o, const int* frozen, hipStream_t st) {
+  const Plan pl = make_plan(lat, L, PL, n, C, o.threads);
   dim3 blk(pl.nchunk, pl.S);
   dim3 grd(pl.nblocks);
   const void* U;
@@ -1001,7 +1042,7 @@ static int dslash_dispatch_order(const mbbs_lattice_s* lat, int L, int order, bo
   using EO = typename Store<POUT>::Elem;
   using EL = LinkElem<PL>;
   GeomK gk = lat->gk;
-  gk.nt_store = lat->nt_store[PL];
+  gk.nt_store = o.nt;
 #define MBBS_LAUNCH(ORD, BLK)                                                                   \
   hipLaunchKernelGGL((k_dslash<PIN, POUT, PL, C, ORD, BLK>), grd, blk, (size_t)lat->lds_pad_kb * 1024, st,     \
                      gk, lat->kappa, L,                                                                     \
@@ -1010,7 +1051,7 @@ static int dslash_dispatch_order(const mbbs_lattice_s* lat, int L, int order, bo
     if (blocked) MBBS_LAUNCH(LEX, true);
     else if (C <= 2 && L == 12) {   // the common block width, with compile-time element offsets
       if constexpr (C <= 2) {
-        if (lat->hop_pair[PL])
+        if (o.pair)
           hipLaunchKernelGGL((k_dslash<PIN, POUT, PL, C, LEX, false, true, 12>), grd, blk,
                              (size_t)lat->lds_pad_kb * 1024, st, gk, lat->kappa, L, (const EI*)in, in_s, (EO*)out,
                              out_s, (const EL*)U, s0, n, pl.bpt, pl.ngroups, frozen);
@@ -1019,7 +1060,7 @@ static int dslash_dispatch_order(const mbbs_lattice_s* lat, int L, int order, bo
                              (size_t)lat->lds_pad_kb * 1024, st, gk, lat->kappa, L, (const EI*)in, in_s, (EO*)out,
                              out_s, (const EL*)U, s0, n, pl.bpt, pl.ngroups, frozen);
       }
-    } else if (lat->hop_pair[PL])
+    } else if (o.pair)
       hipLaunchKernelGGL((k_dslash<PIN, POUT, PL, C, LEX, false, true>), grd, blk, (size_t)lat->lds_pad_kb * 1024, st,
                          gk, lat->kappa, L, (const EI*)in, in_s, (EO*)out, out_s, (const EL*)U, s0, n, pl.bpt,
                          pl.ngroups, frozen);
@@ -1036,14 +1077,17 @@ template <int PIN, int POUT, int PL>
 static int dslash_dispatch_c(const mbbs_lattice_s* lat, int L, int order, bool blocked,
                              const void* in, const float* in_s, void* out, float* out_s, int s0,
                              int n, const int* frozen, hipStream_t st) {
+  const OpSetting o = op_setting(lat, L, PL, order == LEX && !blocked && s0 == 0 && n == lat->g.V);
   if constexpr (PIN == POUT && PIN == PL) {
     TileArgs T;
     const bool whole = order == LEX ? (s0 == 0 && n == lat->g.V) : (s0 % lat->g.Vb == 0 && n % lat->g.Vb == 0);
     // the tiled kernels move two FP32 columns as one 16-byte access: both
     // fields 16-byte aligned, else the column-by-column kernel below
     const bool al = (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
-    if (whole && al && tile_plan(lat, L, PL, &T))
+    if (whole && al && (o.tile > 0 ? tile_plan_on(lat, L, PL, &T) : o.tile < 0 && tile_plan(lat, L, PL, &T))) {
+      if (o.tile > 0) T.nt = o.nt;
       return launch_dslash_tiled(lat, L, PL, order, blocked, T, in, in_s, out, out_s, s0, n, frozen, st);
+    }
   }
   const int P = lat->nsys == 1 ? lat->split[PL] : 0;   // the split kernels serve single systems only
   if ((P == 2 || P == 4) && !lat->gk.clov) {   // the split kernels have no clover step
@@ -1053,11 +1097,11 @@ static int dslash_dispatch_c(const mbbs_lattice_s* lat, int L, int order, bool b
       return dslash_split_launch<PIN, POUT, PL, 2>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, S, frozen, st);
     }
   }
-  switch (pick_chunk(lat, L, PL)) {
-    case 4: return dslash_dispatch_order<PIN, POUT, PL, 4>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, frozen, st);
-    case 3: return dslash_dispatch_order<PIN, POUT, PL, 3>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, frozen, st);
-    case 2: return dslash_dispatch_order<PIN, POUT, PL, 2>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, frozen, st);
-    default: return dslash_dispatch_order<PIN, POUT, PL, 1>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, frozen, st);
+  switch (o.C) {
+    case 4: return dslash_dispatch_order<PIN, POUT, PL, 4>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, o, frozen, st);
+    case 3: return dslash_dispatch_order<PIN, POUT, PL, 3>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, o, frozen, st);
+    case 2: return dslash_dispatch_order<PIN, POUT, PL, 2>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, o, frozen, st);
+    default: return dslash_dispatch_order<PIN, POUT, PL, 1>(lat, L, order, blocked, in, in_s, out, out_s, s0, n, o, frozen, st);
   }
 }
 

@@ -136,6 +136,8 @@ struct mbbs_lattice_s {
   int tile[3] = {0, 0, 0};      // LDS-tiled operator and MR kernels: 0 off, 1 on, 2 on with the MR update fused,
                                 // 3 on with tiles of at most half the LDS
   int tile_lg[3] = {0, 0, 0};   // columns per tiled workgroup (0: all L)
+  int ncu = 0;                  // compute units of the device
+  bool op_set[3] = {false, false, false};   // an operator setting of the precision was chosen by the caller
   int mr_once[3] = {0, 0, 0};   // MR domain solves form psi once from r_0 and the steps' A r (1) or step by step (0)
   // SSOR wavefront order inside a domain: local indices sorted by the
   // hyperplane h = l_0 + l_1 + l_2 + l_3 (then by local index); hyperplane h

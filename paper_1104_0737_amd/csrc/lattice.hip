@@ -223,6 +223,7 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
   lat->kappa = kappa[0];
   lat->nsys = nsys;
   (void)hipGetDevice(&lat->device);
+  (void)hipDeviceGetAttribute(&lat->ncu, hipDeviceAttributeMultiprocessorCount, lat->device);
   hipStream_t st = (hipStream_t)stream;
   const size_t n = (size_t)V * 36, nsys_links = (size_t)Vsys * 36;
   auto fail = [&](int rc) { mbbs_lattice_destroy(lat); return rc; };
@@ -400,44 +401,51 @@ extern "C" int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value) {
     case MBBS_TUNE_GROUP_FP16S:
       MBBS_CHECK(value >= 0 && value <= 64, "column group out of range");
       lat->group_cols[knob] = value;
+      lat->op_set[knob] = true;
       return MBBS_OK;
     case MBBS_TUNE_BLOCK_THREADS:
       MBBS_CHECK(value >= 32 && value <= 256, "threads per block must be in 32..256");
-      for (int p = 0; p < 3; ++p) lat->block_threads[p] = value;
+      for (int p = 0; p < 3; ++p) { lat->block_threads[p] = value; lat->op_set[p] = true; }
       return MBBS_OK;
     case MBBS_TUNE_BLOCK_THREADS_FP64:
     case MBBS_TUNE_BLOCK_THREADS_FP32:
     case MBBS_TUNE_BLOCK_THREADS_FP16S:
       MBBS_CHECK(value >= 32 && value <= 256, "threads per block must be in 32..256");
       lat->block_threads[knob - MBBS_TUNE_BLOCK_THREADS_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_BLOCK_THREADS_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_SPLIT_FP64:
     case MBBS_TUNE_SPLIT_FP32:
     case MBBS_TUNE_SPLIT_FP16S:
       MBBS_CHECK(value == 0 || value == 1 || value == 2 || value == 4, "split must be 0, 1, 2 or 4");
       lat->split[knob - MBBS_TUNE_SPLIT_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_SPLIT_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_PERSIST_BLOCKS:
       MBBS_CHECK(value >= 0 && value <= 16, "persistent blocks per CU must be in 0..16");
       lat->persist_blocks = value;
+      for (bool& o : lat->op_set) o = true;
       return MBBS_OK;
     case MBBS_TUNE_NT_STORE_FP64:
     case MBBS_TUNE_NT_STORE_FP32:
     case MBBS_TUNE_NT_STORE_FP16S:
       MBBS_CHECK(value == 0 || value == 1, "nontemporal store flag must be 0 or 1");
       lat->nt_store[knob - MBBS_TUNE_NT_STORE_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_NT_STORE_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_HOP_PAIR_FP64:
     case MBBS_TUNE_HOP_PAIR_FP32:
     case MBBS_TUNE_HOP_PAIR_FP16S:
       MBBS_CHECK(value == 0 || value == 1, "hop pairing must be 0 or 1");
       lat->hop_pair[knob - MBBS_TUNE_HOP_PAIR_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_HOP_PAIR_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_CHUNK_FP64:
     case MBBS_TUNE_CHUNK_FP32:
     case MBBS_TUNE_CHUNK_FP16S:
       MBBS_CHECK(value >= 0 && value <= 4, "columns per thread must be 0 (automatic) or 1..4");
       lat->chunk[knob - MBBS_TUNE_CHUNK_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_CHUNK_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_TILE_FP64:
     case MBBS_TUNE_TILE_FP32:
@@ -446,12 +454,14 @@ extern "C" int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value) {
       // the folded MR update is withdrawn for FP16 storage: its only run did not finish
       MBBS_CHECK(!(value == 2 && knob == MBBS_TUNE_TILE_FP16S), "folded MR update not available for FP16 storage");
       lat->tile[knob - MBBS_TUNE_TILE_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_TILE_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_TILE_COLS_FP64:
     case MBBS_TUNE_TILE_COLS_FP32:
     case MBBS_TUNE_TILE_COLS_FP16S:
       MBBS_CHECK(value >= 0 && value <= 256, "columns per tiled workgroup must be in 0..256");
       lat->tile_lg[knob - MBBS_TUNE_TILE_COLS_FP64] = value;
+      lat->op_set[knob - MBBS_TUNE_TILE_COLS_FP64] = true;
       return MBBS_OK;
     case MBBS_TUNE_MR_ONCE_FP64:
     case MBBS_TUNE_MR_ONCE_FP32:
@@ -466,6 +476,7 @@ extern "C" int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value) {
     case MBBS_TUNE_LDS_PAD_KB:
       MBBS_CHECK(value >= 0 && value <= 64, "LDS pad must be in 0..64 KiB");
       lat->lds_pad_kb = value;
+      for (bool& o : lat->op_set) o = true;
       return MBBS_OK;
     default:
       set_error("unknown tuning knob");

@@ -551,8 +551,7 @@ static bool ssor_plan(const mbbs_lattice_s* lat, const SapBuffers& b, SsorPlan* 
   if ((size_t)lat->g.V * 4 * (b.prec == P64 ? 9 : 5) >= (1ull << 32)) return false;
   const size_t elem = b.prec == P64 ? 16 : 8;
   auto bytes = [&](int lg) { return 24 * ((size_t)lat->hp_max * lg + 1) * elem; };
-  int ncu = 0;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, lat->device) != hipSuccess) return false;
+  const int ncu = lat->ncu;
   // Both ways round alike, except where the compiler contracts the products of
   // boundary phases or of the clover term: there the rule looks at one system,
   // so that a batch runs its systems as they run alone.

@@ -17,6 +17,7 @@ struct TileArgs {
   int lg;          // columns per workgroup (a divisor of L)
   int ng;          // workgroups per tile: L / lg
   unsigned lds;    // dynamic LDS bytes per workgroup
+  int nt;          // nontemporal output stores (-1: the lattice's setting)
 };
 
 // Columns per thread of the tiled kernels: 1 in FP64, 2 otherwise.
@@ -26,6 +27,8 @@ inline int tile_cols(int prec) { return prec == P64 ? 1 : 2; }
 // on, L fits the kernel's column split, a tile shape fits LDS and one
 // workgroup), with the tile shape in *out.
 bool tile_plan(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out);
+// The same with setting 1 whatever the lattice's.
+bool tile_plan_on(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out);
 
 // out = in - kappa H in on sites [s0, s0 + n) of order `order` (whole domains;
 // LEX: the whole lattice), all hops or in-domain hops only (blocked); input

@@ -552,6 +552,7 @@ bool pick_tile(const mbbs_lattice_s* lat, int L, size_t es, int C, bool scaled, 
     if (lds + 256 * sizeof(int) > 160 * 1024 / (size_t)cap) continue;
     if ((12 * L * es) % 16) continue;
     TileArgs T;
+    T.nt = -1;
     T.lg = lg;
     T.ng = L / lg;
     for (int m = 0; m < 4; ++m) {
@@ -587,7 +588,7 @@ int launch_tile_t(const mbbs_lattice_s* lat, int L, const TileArgs& T, const voi
   using EO = typename Store<PO>::Elem;
   using EL = LinkElem<PL>;
   GeomK gk = lat->gk;
-  gk.nt_store = lat->nt_store[PL];
+  gk.nt_store = T.nt >= 0 ? T.nt : lat->nt_store[PL];
   const dim3 blk(T.ts * (T.lg / C)), grd(ntiles * T.ng);
   if (L == 12 && T.lg == 12) {
     auto fn = k_tile<P, PL, C, ORDER, HOPS, OP, 12, 12, PPSI, PO>;
@@ -635,6 +636,10 @@ bool tile_plan(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out) {
   if (lat->tile[prec] < 1) return false;
   return pick_tile(lat, L, elem_bytes(prec), tile_cols(prec), prec == P16, tile_cap(lat, prec), lat->tile_lg[prec],
                    out);
+}
+
+bool tile_plan_on(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out) {
+  return pick_tile(lat, L, elem_bytes(prec), tile_cols(prec), prec == P16, 1, 0, out);
 }
 
 bool tile_plan_resid(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out) {
