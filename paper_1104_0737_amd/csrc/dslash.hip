@@ -209,18 +209,13 @@ __global__ void __launch_bounds__(256) k_mr_dslash(GeomK k, double kappa, int L,
   }
 }
 
-// MR step, part 1b: per domain of the colour (one block each), sum the block
-// partials in fixed order and form omega = <w, r> / <w, w> (0 if <w, w> = 0).
-// A separate launch: the kernel boundary makes every block's partial visible
-// without device-wide fences (which on this chip write back and invalidate the
-// per-XCD L2 caches).
-__global__ void __launch_bounds__(256) k_mr_omega(GeomK k, int L, int nblk, const double* __restrict__ partial,
-                                                  double* __restrict__ omega, const int* __restrict__ frozen) {
-  const int dom = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
-  if (sys_frozen(k, frozen, sys_of_domain(k, dom))) return;
-  __shared__ double red[3 * 256];
-  const int G = nthr / L > 0 ? nthr / L : 1;
-  const double* pp = partial + ((size_t)dom * nblk) * L * 3;
+// A domain's <w, r> and <w, w> per column from its nblk blocks' partials, in an
+// order that does not depend on the block's threads, and omega = <w, r> / <w, w>
+// (0 if <w, w> = 0) of column col through put(col, re, im).  red: 3 * 256.
+template <typename F>
+__device__ __forceinline__ void domain_omega(int L, int nblk, const double* __restrict__ pp, double* red, int tid,
+                                             int nthr, F put) {
+  const int G = 256 / L > 0 ? 256 / L : 1;
   for (int e = tid; e < G * L; e += nthr) {
     const int g = e / L, col = e % L;
     double a0 = 0, a1 = 0, a2 = 0;
@@ -243,13 +238,31 @@ __global__ void __launch_bounds__(256) k_mr_omega(GeomK k, int L, int nblk, cons
     }
     double o_re = 0, o_im = 0;
     if (s2 > 0) { o_re = s0 / s2; o_im = s1 / s2; }
-    omega[((size_t)dom * L + col) * 2 + 0] = o_re;
-    omega[((size_t)dom * L + col) * 2 + 1] = o_im;
+    put(col, o_re, o_im);
   }
 }
 
+// MR step, part 1b: omega per domain of the colour (one block each).
+// A separate launch: the kernel boundary makes every block's partial visible
+// without device-wide fences (which on this chip write back and invalidate the
+// per-XCD L2 caches).
+__global__ void __launch_bounds__(256) k_mr_omega(GeomK k, int L, int nblk, const double* __restrict__ partial,
+                                                  double* __restrict__ omega, const int* __restrict__ frozen) {
+  const int dom = blockIdx.x;
+  if (sys_frozen(k, frozen, sys_of_domain(k, dom))) return;
+  __shared__ double red[3 * 256];
+  domain_omega(L, nblk, partial + ((size_t)dom * nblk) * L * 3, red, threadIdx.x, blockDim.x,
+               [&](int col, double re, double im) {
+                 omega[((size_t)dom * L + col) * 2 + 0] = re;
+                 omega[((size_t)dom * L + col) * 2 + 1] = im;
+               });
+}
+
 // MR step, part 2: psi += omega r ; r -= omega w  (per domain and column).
-template <int PR, int PPSI>
+// SUMS: omega is given as the domain's nblk block partials, which every block
+// (its sites lie in one domain) sums for itself: a launch less where they are
+// few (MR_OMEGA_HERE).
+template <int PR, int PPSI, bool SUMS = false>
 __global__ void __launch_bounds__(256) k_mr_update(GeomK k, int L, int s0, int n,
                                                    typename Store<PR>::Elem* __restrict__ r,
                                                    float* __restrict__ r_s,
@@ -257,18 +270,29 @@ __global__ void __launch_bounds__(256) k_mr_update(GeomK k, int L, int s0, int n
                                                    const float* __restrict__ w_s,
                                                    typename Store<PPSI>::Elem* __restrict__ psi,
                                                    const double* __restrict__ omega, int update_r,
-                                                   int assign, const int* __restrict__ frozen) {
+                                                   int assign, const int* __restrict__ frozen, int nblk = 0) {
   using R = typename Store<PR>::Real;
   const int s = s0 + xcd_block(blockIdx.x, gridDim.x) * blockDim.y + threadIdx.y;
   if (s >= s0 + n) return;
   const int col = threadIdx.x;
   const int dom = (s - (s >= k.g.Vh ? k.g.Vh : 0)) / k.g.Vb;
   if (sys_frozen(k, frozen, sys_of_domain(k, dom))) return;
-  const cplx<R> om = cmake<R>((R)omega[((size_t)dom * L + col) * 2], (R)omega[((size_t)dom * L + col) * 2 + 1]);
   const size_t base = (size_t)s * 12 * L + col;
   const size_t sidx = (size_t)s * L + col;
   cplx<R> rv[4][3];
   load_spinor<PR, R>(r, r_s, base, L, sidx, rv);
+  const double* oc = omega + ((size_t)dom * L + col) * 2;
+  if constexpr (SUMS) {
+    __shared__ double red[3 * 256], oms[2 * 64];
+    domain_omega(L, nblk, omega + ((size_t)dom * nblk) * L * 3, red, threadIdx.y * L + col, L * blockDim.y,
+                 [&](int c, double re, double im) {
+                   oms[2 * c] = re;
+                   oms[2 * c + 1] = im;
+                 });
+    __syncthreads();
+    oc = oms + 2 * col;
+  }
+  const cplx<R> om = cmake<R>((R)oc[0], (R)oc[1]);
 #pragma unroll
   for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -920,9 +944,6 @@ static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites, in
   p.nblocks = (nsites / lat->g.Vb) * p.ngroups * p.bpt;
   return p;
 }
-static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites) {
-  return make_plan(lat, L, prec, nsites, pick_chunk(lat, L, prec), lat->block_threads[prec]);
-}
 
 // How the operator runs: LDS-tiled or one thread per site and C columns.
 struct OpSetting { int tile, C, threads, pair, nt; };
@@ -1214,6 +1235,18 @@ static bool use_mr_fused(const mbbs_lattice_s* lat, int L) {
   return (size_t)lat->g.Vb * L <= 2048;
 }
 
+// Partials (blocks x L) of a domain up to which the MR update sums them itself
+// instead of k_mr_omega before it.
+constexpr int MR_OMEGA_HERE = 1024;
+
+// Threads per block of the SAP stencils: 64 instead of 256 where 256 leave CUs
+// without a block (FP16S, 12^4, L = 6, 4 cycles of 4 steps: 1179 -> 966 us; 16^3 x
+// 32, L = 12 fills them: 3803, 4025 with 64), unless the caller chose.
+static int sap_threads(const mbbs_lattice_s* lat, int L, int prec) {
+  const size_t n = (size_t)lat->g.Vh / lat->nsys * L / pick_chunk(lat, L, prec);
+  return !lat->op_set[prec] && (n + 255) / 256 <= (size_t)lat->ncu ? 64 : lat->block_threads[prec];
+}
+
 template <int PR, int PPSI, int PL>
 static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, int nmr,
                       const int* frozen, hipStream_t st, Profiler* prof) {
@@ -1223,7 +1256,7 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
   const int L = b.L;
   const Geom& g = lat->g;
   const EL* U = PL == P64 ? (const EL*)lat->U64dm : PL == P32 ? (const EL*)lat->U32dm : (const EL*)lat->U16dm;
-  const Plan pl = make_plan(lat, L, PL, g.Vh);
+  const Plan pl = make_plan(lat, L, PL, g.Vh, pick_chunk(lat, L, PL), sap_threads(lat, L, PL));
   const int C = pl.C, S = pl.S;
   const int Su = sites_per_block(L, g.Vb);
   const size_t red_bytes = 3 * (size_t)S * pl.gw * sizeof(double);
@@ -1312,7 +1345,9 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
       const bool tiled = ((uintptr_t)b.r & 15) == 0 && ((uintptr_t)b.w & 15) == 0 && tile_plan(lat, L, PL, &T);
       const size_t ostride = (size_t)(g.ndom / 2) * L * 2;   // doubles per step's omega
       // one MR stencil step w = A_DD r on this colour, then its omega (per domain and column) into om
-      auto stencil_step = [&](const void* rr, const float* rr_s, void* ww, float* ww_s, double* om) -> int {
+      // (here: not that, but the count of the domain's partials into *here, where the update may sum them)
+      auto stencil_step = [&](const void* rr, const float* rr_s, void* ww, float* ww_s, double* om,
+                              int* here = nullptr) -> int {
         int nblk_dom = g.Vb / S;
         if (tiled) {
           nblk_dom = T.tpd;
@@ -1359,6 +1394,8 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
 #undef MRD
         }
         MBBS_HIP(hipGetLastError());
+        if (here) *here = nblk_dom * L <= MR_OMEGA_HERE ? nblk_dom : 0;
+        if (here && *here) return MBBS_OK;
         hipLaunchKernelGGL(k_mr_omega, dim3(g.ndom / 2), dim3(256), 0, st, lat->gk, L, nblk_dom,
                            (const double*)b.partial, om, frozen);
         MBBS_HIP(hipGetLastError());
@@ -1451,7 +1488,7 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
                              n, (float4*)rb[c], (const float4*)wb[c], (float4*)b.psi, b.omega, 0, assign, frozen);
         } else {
           hipLaunchKernelGGL((k_mr_update<PR, PPSI>), dim3(ceil_div(n, Su)), dim3(L, Su), 0, st, lat->gk, L, s0, n,
-                             (ER*)rb[c], rbs[c], (const ER*)wb[c], wbs[c], (EP*)b.psi, b.omega, 0, assign, frozen);
+                             (ER*)rb[c], rbs[c], (const ER*)wb[c], wbs[c], (EP*)b.psi, b.omega, 0, assign, frozen, 0);
         }
         if (prof) prof->end();
         MBBS_HIP(hipGetLastError());
@@ -1459,24 +1496,24 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
       }
       for (int it = 0; it < nmr; ++it) {
         if (prof) prof->begin(MBBS_K_MR_DSLASH);
-        MBBS_TRY(stencil_step(b.r, b.r_s, b.w, b.w_s, b.omega));
+        const bool flat = PR == P32 && PPSI == P32 && L % 2 == 0;
+        int here = 0;
+        MBBS_TRY(stencil_step(b.r, b.r_s, b.w, b.w_s, b.omega, flat ? nullptr : &here));
         if (prof) prof->end();
         if (prof) prof->begin(MBBS_K_MR_UPDATE);
-        if constexpr (PR == P32 && PPSI == P32) {
-          if (L % 2 == 0) {
-            const size_t npair = (size_t)n * 6 * L;
-            hipLaunchKernelGGL(k_mr_update_flat, dim3((unsigned)((npair + 255) / 256)), dim3(256), 0, st, lat->gk,
-                               L, s0, n, (float4*)b.r, (const float4*)b.w, (float4*)b.psi, b.omega,
-                               (int)(it + 1 < nmr), (int)(cy == 0 && it == 0), frozen);
-          } else {
-            hipLaunchKernelGGL((k_mr_update<PR, PPSI>), dim3(ceil_div(n, Su)), dim3(L, Su), 0, st, lat->gk, L, s0,
-                               n, (ER*)b.r, b.r_s, (const ER*)b.w, b.w_s, (EP*)b.psi, b.omega,
-                               (int)(it + 1 < nmr), (int)(cy == 0 && it == 0), frozen);
-          }
+        if (here) {
+          hipLaunchKernelGGL((k_mr_update<PR, PPSI, true>), dim3(ceil_div(n, Su)), dim3(L, Su), 0, st, lat->gk, L, s0,
+                             n, (ER*)b.r, b.r_s, (const ER*)b.w, b.w_s, (EP*)b.psi, b.partial,
+                             (int)(it + 1 < nmr), (int)(cy == 0 && it == 0), frozen, here);
+        } else if (flat) {
+          const size_t npair = (size_t)n * 6 * L;
+          hipLaunchKernelGGL(k_mr_update_flat, dim3((unsigned)((npair + 255) / 256)), dim3(256), 0, st, lat->gk, L, s0,
+                             n, (float4*)b.r, (const float4*)b.w, (float4*)b.psi, b.omega, (int)(it + 1 < nmr),
+                             (int)(cy == 0 && it == 0), frozen);
         } else {
           hipLaunchKernelGGL((k_mr_update<PR, PPSI>), dim3(ceil_div(n, Su)), dim3(L, Su), 0, st, lat->gk, L, s0,
                              n, (ER*)b.r, b.r_s, (const ER*)b.w, b.w_s, (EP*)b.psi, b.omega,
-                             (int)(it + 1 < nmr), (int)(cy == 0 && it == 0), frozen);
+                             (int)(it + 1 < nmr), (int)(cy == 0 && it == 0), frozen, 0);
         }
         if (prof) prof->end();
         MBBS_HIP(hipGetLastError());

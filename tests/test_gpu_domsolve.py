@@ -125,3 +125,17 @@ def test_two_streams_and_graph_replays():
             g.replay()
             assert gu.host(Y[0]).tobytes() == ref[0].tobytes()
             assert gu.host(_apply(lat.h, X[1], 2, 3, 1, ws[0])).tobytes() == ref[1].tobytes()
+
+
+@pytest.mark.parametrize("prec,L", [(0, 12), (1, 15)])
+def test_omega_summed_in_the_update(prec, L):
+    """The launches per MR step: few block partials of a domain are summed by the
+    update, many (small blocks) by a launch of their own."""
+    dims, block = (8, 8, 8, 8), (4, 4, 4, 4)
+    with gu.Lattice(dims, block, inputs.gauge_field(dims, 0.3, 660), 0.12) as lat:
+        X = gu.dev(inputs.gaussian_block(4096, L, 661))
+        B.mbbs_lattice_tune(lat.h, B.TUNE_MR_FUSED, 0)
+        Y = gu.host(_apply(lat.h, X, 2, 4, prec))
+        B.mbbs_lattice_tune(lat.h, B.TUNE_BLOCK_THREADS, 32)
+        S = gu.host(_apply(lat.h, X, 2, 4, prec))
+    assert np.all(gu.rel_col_err(Y, S) <= PAIR_TOL[prec]), gu.rel_col_err(Y, S)
