@@ -115,8 +115,9 @@ int launch_loop_test(int L, const SolverDev& d, hipStream_t st, int nsys = 1);
 // b = a on n_per_sys entries of every system whose flag is clear.
 int launch_copy_sys(const double2* a, double2* b, size_t n_per_sys, const int* frozen, hipStream_t st, SysBatch sb);
 int launch_fill(double2* p, size_t n, double2 v, hipStream_t st);
-int launch_chol_standalone(int L, const double2* G, double2* gam, double2* ginv, int* ok, hipStream_t st);
-int launch_matmul_small(int L, const double2* A, const double2* B, double2* C, hipStream_t st);
+int launch_chol_standalone(int L, const double2* G, double2* gam, double2* ginv, const int* prev, int* bad,
+                           hipStream_t st);
+int launch_matmul_small(int L, const double2* A, const double2* B, double2* C, const int* bad, hipStream_t st);
 int launch_lu_standalone(int L, int m, const double2* G, const double2* R, double2* X, int* ok, hipStream_t st);
 int launch_copy(const double2* a, double2* b, size_t n, hipStream_t st);
 

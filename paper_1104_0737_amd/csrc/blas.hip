@@ -731,23 +731,25 @@ int launch_convert_from(int prec, size_t nsites, int L, const void* x, const flo
 namespace mbbs {
 
 // Standalone Cholesky factor + inverse (for the CholQR entry point):
-// G (in) -> gamma (out, upper) and ginv; *ok = 0 if not positive definite.
+// G (in) -> gamma (out, upper) and ginv; *bad = 1, and nothing else written, if
+// not positive definite or if an earlier pass was not (*prev).
 __global__ void k_chol_standalone(int L, const double2* __restrict__ G, double2* __restrict__ gam,
-                                  double2* __restrict__ ginv, int* __restrict__ ok) {
+                                  double2* __restrict__ ginv, const int* __restrict__ prev, int* __restrict__ bad) {
   extern __shared__ double2 sm[];
   double2* A = sm;
   double2* gi = sm + L * L;
   for (int e = threadIdx.x; e < L * L; e += blockDim.x) A[e] = G[e];
   __syncthreads();
-  bool good = chol_inv(L, A, gi);
-  if (threadIdx.x == 0) *ok = good ? 1 : 0;
+  const bool good = chol_inv(L, A, gi) && !(prev && *prev);
+  if (threadIdx.x == 0) *bad = good ? 0 : 1;
   if (!good) return;
   for (int e = threadIdx.x; e < L * L; e += blockDim.x) { gam[e] = A[e]; ginv[e] = gi[e]; }
 }
 
-// gam_out = g2 * g1 (combined R factor of two CholQR passes).
+// gam_out = g2 * g1 (combined R factor of two CholQR passes), unless *bad.
 __global__ void k_matmul_small(int L, const double2* __restrict__ A, const double2* __restrict__ B,
-                               double2* __restrict__ C) {
+                               double2* __restrict__ C, const int* __restrict__ bad) {
+  if (*bad) return;
   for (int e = threadIdx.x; e < L * L; e += blockDim.x) {
     int i = e / L, j = e % L;
     cplx<double> s = cmake(0.0, 0.0);
@@ -773,13 +775,15 @@ __global__ void k_lu_standalone(int L, int m, const double2* __restrict__ G, con
   for (int e = threadIdx.x; e < L * m; e += blockDim.x) X[e] = Xs[e];
 }
 
-int launch_chol_standalone(int L, const double2* G, double2* gam, double2* ginv, int* ok, hipStream_t st) {
-  hipLaunchKernelGGL(k_chol_standalone, dim3(1), dim3(64), 2 * (size_t)L * L * sizeof(double2), st, L, G, gam, ginv, ok);
+int launch_chol_standalone(int L, const double2* G, double2* gam, double2* ginv, const int* prev, int* bad,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(k_chol_standalone, dim3(1), dim3(64), 2 * (size_t)L * L * sizeof(double2), st, L, G, gam, ginv,
+                     prev, bad);
   MBBS_HIP(hipGetLastError());
   return MBBS_OK;
 }
-int launch_matmul_small(int L, const double2* A, const double2* B, double2* C, hipStream_t st) {
-  hipLaunchKernelGGL(k_matmul_small, dim3(1), dim3(256), 0, st, L, A, B, C);
+int launch_matmul_small(int L, const double2* A, const double2* B, double2* C, const int* bad, hipStream_t st) {
+  hipLaunchKernelGGL(k_matmul_small, dim3(1), dim3(256), 0, st, L, A, B, C, bad);
   MBBS_HIP(hipGetLastError());
   return MBBS_OK;
 }
