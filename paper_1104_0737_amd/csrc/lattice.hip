@@ -321,7 +321,8 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
         set_error("wavefront table copy failed");
         return fail(MBBS_EHIP);
       }
-      link_planes(lat, lat->hp_loc, lat->Uhp, st);
+      // (read only where a colour's domains leave CUs idle: ssor.hip)
+      if (g.ndom / 2 / nsys <= lat->ncu / 2) link_planes(lat, lat->hp_loc, lat->Uhp, st);
       if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
         set_error("link conversion failed");
         return fail(MBBS_EHIP);
