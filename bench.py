@@ -28,6 +28,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Dslash site·RHS/s (HBM GB/s) + time-to-solution/RHS, mixed vs FP64 @1e-10"
 HBM_PEAK_GBS = 8000.0
+VECTOR_PEAK_TFLOPS = 78.6   # FP32 FMA: 256 CUs x 4 SIMDs x 16 lanes x 2 x 2.4 GHz (packed forms not used)
 
 
 def parse():
@@ -90,6 +91,11 @@ def algorithmic_bytes(cls, L, dims, block, ncy, nmr, sap_prec="fp32", nssor=1, c
     sap_resid  one colour: read eta, write r; except on the first half-sweep
                also read psi on the colour and on the other colour's sites
                that touch it (a fraction f of them), and 4 links per site.
+    mr_chip    one colour, the whole domain solve in one launch (timed as
+               mr_dslash when no sap_resid or mr_update launch is): read eta,
+               write psi, 4 links per site; except on the first half-sweep
+               also the other colour's sites that touch the colour, and from
+               the second cycle on read psi.
     ssor       one colour, all sweeps, SAP residual included: N_SSOR = 1 moves
                10 storage fields (eta->a, a->b, a,b->r,a, a->b), psi (the
                residual's stencil as in sap_resid, then read + write, assign
@@ -132,6 +138,11 @@ def algorithmic_bytes(cls, L, dims, block, ncy, nmr, sap_prec="fp32", nssor=1, c
         tot += 2 * (ncy - 1) * Vh * (2 * sp + (1 + f) * ps + 4 * lk)
         tot += (2 * ncy - 1) * Vh * cl                   # every half-sweep but the first
         return tot / (2 * ncy - (1 if once else 0))
+    if cls == "mr_chip":
+        inner = int(np.prod([b - 2 for b in block]))
+        f = 1 - inner / int(np.prod(block))
+        first = 2 * (sp + ps + 4 * lk) + f * ps + cl * 2
+        return Vh * (first + 2 * (ncy - 1) * (sp + (2 + f) * ps + 4 * lk + cl)) / (2 * ncy)
     if cls == "ssor":
         # the SAP residual is formed inside the first sweep
         inner = int(np.prod([b - 2 for b in block]))
@@ -146,6 +157,15 @@ def algorithmic_bytes(cls, L, dims, block, ncy, nmr, sap_prec="fp32", nssor=1, c
                 tot += Vh * (fields * sp + resid + upd + sweeps * (4 * lk + cl))
         return tot / (2 * ncy)
     return None
+
+
+def chip_flops(L, dims, ncy, nmr):
+    """Floating-point operations of one whole-domain launch (mean over a SAP
+    application): 1320 per site and column and stencil (residual, but for the
+    first launch, and one per MR step), and per step w = r - kappa H r (48), the
+    sums (144) and the updates of r and psi (192)."""
+    Vh = int(np.prod(dims)) // 2
+    return Vh * L * (1320 * (nmr + 1 - 1 / (2 * ncy)) + 384 * nmr)
 
 
 def measured_traffic(cls, dims, L, sap_prec, clover=False):
@@ -410,7 +430,8 @@ def main():
         sset = tuning.get(args.sap_prec, {}).get("sap", {}).get("setting", [])
         once = len(sset) > 7 and sset[7] == 1
         tiled = len(sset) > 6 and sset[6] >= 1
-        byl = algorithmic_bytes(dominant, L, dims, cfg.block, cfg.ncy, cfg.nmr, args.sap_prec, args.nssor,
+        chip = dominant == "mr_dslash" and kl["sap_resid"] == 0 and kl["mr_update"] == 0
+        byl = algorithmic_bytes("mr_chip" if chip else dominant, L, dims, cfg.block, cfg.ncy, cfg.nmr, args.sap_prec, args.nssor,
                                 bool(args.csw), once, tiled)
         avg_ms = km[dominant] / kl[dominant]
         ach = byl / (avg_ms * 1e-3) / 1e9
@@ -419,8 +440,14 @@ def main():
                 "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "traffic_over_algorithmic": round(traffic / byl, 3) if traffic else None,
                 "bytes_per_launch": byl, "avg_launch_ms": avg_ms, "launches": kl[dominant],
-                "sap_tiled": tiled, "sap_psi_once": once,
+                "sap_tiled": tiled and not chip, "sap_psi_once": once and not chip,
                 "class_ms": {k: round(v, 3) for k, v in km.items()}}
+
+        if chip:   # the domain stays on the chip: vector arithmetic, not HBM, is the nearer bound
+            tf = chip_flops(L, dims, cfg.ncy, cfg.nmr) / (avg_ms * 1e-3) / 1e12
+            roof.update({"kernel": "mr_dslash (whole domain solve)", "bound": "fp32 vector",
+                         "achieved": round(tf, 2), "peak": VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
+                         "frac": round(tf / VECTOR_PEAK_TFLOPS, 4), "hbm_gbs": round(ach, 1)})
 
     cpu = None
     if not args.no_cpu_baseline:
