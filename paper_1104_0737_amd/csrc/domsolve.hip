@@ -970,8 +970,11 @@ int launch_dom_ts(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
   // idempotent; the call is cheap beside the launch
   MBBS_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   const int grid = p.G == 1 ? p.units : p.ngroups * p.G;
-  // one thread per (site, column chunk), and per entry of the staged faces
-  const int thr = (std::max({p.T, p.H, 2 * (p.n[0] + p.n[1]), 2 * (p.n[2] + p.n[3])}) + 63) / 64 * 64;
+  // one thread per (site, column chunk), per entry of the staged faces, and 16
+  // per column for the domain sums (the most where a domain has few sites; lg is
+  // at most 16, so TS holds them)
+  const int thr = (std::max({p.T, p.H, 2 * (p.n[0] + p.n[1]), 2 * (p.n[2] + p.n[3]), 16 * p.lg}) + 63) / 64 * 64;
+  MBBS_CHECK(thr <= TS, "domain solve: more threads than LDS cells per row");
   DomArgs a{};
   a.P = p;
   a.sy = sy;

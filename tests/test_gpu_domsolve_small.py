@@ -1,0 +1,41 @@
+"""SAP with MR domain solves on domains of one to sixteen sites, which one
+workgroup holds with room to spare, against the oracle.
+
+The extents of 1 leave a domain few or no hops of its own; 4, 8 and 16 columns
+of such a domain share a workgroup, whose domain sums take 16 lanes per column
+whatever the number of sites.  Tolerances: the oracle's as for the other SAP
+kernels.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import sap
+from paper_1104_0737_amd import inputs
+
+pytestmark = pytest.mark.gpu
+gu = pytest.importorskip("tests.gpu_util")
+torch = gu.torch
+B = gu.binding
+
+PH_TWIST = ((np.cos(0.3), np.sin(0.3)), (1.0, 0.0), (np.cos(1.1), -np.sin(1.1)), (-1.0, 0.0))
+SAP_TOL = {0: 1e-12, 1: 3e-5}
+
+
+@pytest.mark.parametrize("dims,block,L", [
+    ((8, 8, 8, 8), (1, 1, 1, 1), 8), ((8, 8, 8, 8), (1, 1, 1, 1), 16), ((8, 8, 8, 8), (2, 1, 1, 1), 8),
+    ((8, 8, 8, 8), (2, 2, 1, 1), 16), ((8, 8, 8, 16), (2, 2, 2, 1), 16), ((8, 8, 16, 16), (2, 2, 2, 2), 16)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_parity(dims, block, L, prec):
+    gu.flush(f"sap on small domains {dims} {block} L={L} prec={prec}")
+    V = int(np.prod(dims))
+    U = inputs.gauge_field(dims, 0.3, 612)
+    eta = inputs.gaussian_block(V, L, 613)
+    with gu.Lattice(dims, block, U, 0.12, PH_TWIST) as lat:
+        ws = torch.empty(B.mbbs_sap_workspace_size(lat.h, L, prec), dtype=torch.uint8, device="cuda")
+        Y = torch.empty((12 * V, L), dtype=torch.complex128, device="cuda")
+        B.mbbs_sap_apply(lat.h, L, gu.dev(eta), Y, 2, 3, prec, ws)
+        Y = gu.host(Y)
+    ref = sap.sap(U, 0.12, PH_TWIST, sap.Domains(dims, block), eta, 2, 3).reshape(12 * V, L)
+    assert np.all(gu.rel_col_err(Y, ref) <= SAP_TOL[prec]), gu.rel_col_err(Y, ref)
+    assert np.all(gu.max_elem_err(Y, ref) <= SAP_TOL[prec])
