@@ -209,6 +209,12 @@ int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value);
  * host memory of 4 ints.  Errors: EINVAL. */
 int mbbs_lattice_tile_shape(mbbs_lattice_t lat, int L, int prec, int32_t* t4);
 
+/* Bound of the waits between workgroups that share a SAP domain on the chip
+ * (MBBS_TUNE_MR_FUSED -1): polls of about a microsecond each, 0..2^30, 2^24 by
+ * default.  A wait that gives up turns the whole result of its SAP application
+ * into NaN.  See mbbs_sap_apply for when one could.  Errors: EINVAL. */
+int mbbs_lattice_sap_polls(mbbs_lattice_t lat, int polls);
+
 /* O(a)-improved (clover) Wilson operator with Jacobi preconditioning (Sec. 2.2:
  * the matrix is divided by I + clover term before the domain decomposition).
  * The clover term, built on the device from the lattice's links and kappa, is
@@ -269,7 +275,15 @@ int mbbs_apply_blocked(mbbs_lattice_t lat, int L, const double* X_dev, double* Y
  * ws_dev must hold mbbs_sap_workspace_size bytes (caller-owned).  The size
  * depends on the lattice's MBBS_TUNE_TILE_* setting of `prec` (2: two more
  * fields); a workspace sized without it still serves (the MR steps then run
- * unfolded). */
+ * unfolded).
+ * Where workgroups share a domain on the chip (FP64 and FP32, a domain of more
+ * than 256 (site, column) items, MBBS_TUNE_MR_FUSED -1) they wait for each
+ * other.  Eight such launches at once always make progress on a device whose
+ * compute units they may all use (a process has four hardware queues unless
+ * GPU_MAX_HW_QUEUES says otherwise).  With more at once, or on a stream
+ * restricted to a few compute units, a wait may last until its bound
+ * (mbbs_lattice_sap_polls, about 20 s); all of Y is NaN then, and a solve ends
+ * with EBREAKDOWN.  MBBS_TUNE_MR_FUSED 0 runs without such waits. */
 int mbbs_sap_workspace_size(mbbs_lattice_t lat, int L, int prec, size_t* bytes);
 int mbbs_sap_apply(mbbs_lattice_t lat, int L, const double* X_dev, double* Y_dev,
                    int ncy, int nmr, int prec, void* ws_dev, size_t ws_bytes, void* stream);

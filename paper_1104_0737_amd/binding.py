@@ -25,6 +25,7 @@ KERNEL_CLASSES = ("dslash64", "sap_resid", "mr_dslash", "mr_update", "convert", 
 
 EXPORTS = (
     "mbbs_lattice_create", "mbbs_lattice_create_batch", "mbbs_lattice_nsys", "mbbs_lattice_destroy", "mbbs_lattice_tune", "mbbs_lattice_tile_shape",
+    "mbbs_lattice_sap_polls",
     "mbbs_lattice_set_clover",
     "mbbs_lattice_clover_inverse", "mbbs_apply_clover_inverse", "mbbs_lattice_table_size",
     "mbbs_lattice_table",
@@ -84,6 +85,7 @@ def lib():
             "mbbs_lattice_destroy": (i, [vp]),
             "mbbs_lattice_tune": (i, [vp, i, i]),
             "mbbs_lattice_tile_shape": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int32)]),
+            "mbbs_lattice_sap_polls": (i, [vp, i]),
             "mbbs_lattice_set_clover": (i, [vp, d, vp]),
             "mbbs_lattice_clover_inverse": (i, [vp, vp, vp]),
             "mbbs_apply_clover_inverse": (i, [vp, i, vp, vp, vp]),
@@ -216,6 +218,10 @@ def mbbs_lattice_tile_shape(lat, L, prec):
     t = (ctypes.c_int32 * 4)()
     _check(lib().mbbs_lattice_tile_shape(lat, L, prec, t))
     return tuple(t)
+
+
+def mbbs_lattice_sap_polls(lat, polls):
+    return _check(lib().mbbs_lattice_sap_polls(lat, polls))
 
 
 def mbbs_lattice_set_clover(lat, csw, stream=None):

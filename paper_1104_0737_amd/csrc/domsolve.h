@@ -34,11 +34,6 @@ struct DomPlan {
   int ngroups;      // workgroup groups of a launch (G > 1)
 };
 
-// Polls (about a microsecond each) after which a wait for another workgroup
-// gives up: every wait ends.  What it waited for is then missing, so its unit's
-// psi becomes NaN, which the caller's residual shows.
-constexpr int DOM_STEP_POLLS = 1 << 24;
-
 // Whether (and how) SAP with MR domain solves runs on this path for the
 // lattice, L, precision and workspace.
 bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out);
@@ -50,10 +45,11 @@ int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
 
 // FP64 lexicographic block (times gam if given) <-> the storage of `p` in FP64
 // or FP32.  order: the local sites in storage order (null: as the tiles of `p`
-// have them).  dom_to also clears nclear words.
+// have them).  dom_to also clears nclear words; dom_from writes NaN to all of
+// `out` if the word *lost (null: none) is set.
 int dom_to(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const double2* in,
            const double2* gam, void* out, unsigned* clear, int nclear, const int* frozen, hipStream_t st);
 int dom_from(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const void* in,
-             double2* out, const int* frozen, hipStream_t st);
+             double2* out, const int* lost, const int* frozen, hipStream_t st);
 
 }  // namespace mbbs

@@ -21,7 +21,11 @@
 // The groups of G workgroups are formed from tickets in the order in which
 // workgroups start, so only resident workgroups wait for each other: at most
 // G - 1 workgroups of a launch can wait for members that have not started.
-// Every wait is bounded (DOM_STEP_POLLS).
+// Every wait is bounded.  One that gives up sets a word in the workspace: the
+// later launches of the call then do nothing, and the closing conversion writes
+// NaN to the whole result, which a solve reports as a breakdown.  (Marking the
+// unit alone is not enough: its workgroups leave, and the unit that their first
+// member had already claimed would keep what its psi held before.)
 // Faces that carry their own validity (a mark that the reader puts back, no
 // flag) took 6 % off small lattices and added 3 to 8 % to large ones, where the
 // exchange's bandwidth counts; two workgroups of 256 threads per CU instead of
@@ -56,6 +60,7 @@ struct DomSync {
   unsigned long long* flags;  // [group][tile]: tag of the faces published last
   char* slots;                // per group: the tiles' published faces
   size_t slot_bytes;
+  int* lost;                  // set by a wait that gave up
   unsigned tag0;              // first tag of this launch
   int step_polls;
 };
@@ -276,16 +281,17 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
   V* sh = (V*)dom_lds;
   __shared__ double red[3 * 16 * NROW];    // [3][column][row of lanes]
   __shared__ double om_sh[2 * 16];
-  __shared__ int ish[4];                   // group, member, a wait gave up, unit
+  __shared__ int ish[5];                   // group, member, a wait gave up, unit, one gave up in an earlier launch
   const int tid = threadIdx.x;
   const int nthr = blockDim.x;
 
   // ---- the group this workgroup belongs to: tickets are drawn as workgroups
   // start, so a group's members are resident or about to be
   int gid = 0, mem = 0;
-  bool lost = false;   // a wait gave up: psi becomes NaN
+  bool lost = false;   // a wait gave up
   if (A->P.G > 1) {
     if (tid == 0) {
+      ish[4] = __hip_atomic_load(A->sy.lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int t = __hip_atomic_fetch_add(&A->sy.counters[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int g = t / A->P.G;
       ish[0] = g;
@@ -299,7 +305,14 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
     lds_barrier();
     gid = uniform(ish[0]);
     mem = uniform(ish[1]);
+    // (or in this one: the waits of this group's other members end too)
+    if (uniform(ish[4])) return;
   }
+  // a wait gave up
+  auto give_up = [&]() {
+    ish[2] = 1;
+    __hip_atomic_store(A->sy.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   const __amdgpu_buffer_rsrc_t rs = dev_rsrc(A->sy.slots + (size_t)gid * A->sy.slot_bytes, A->sy.slot_bytes);
   unsigned long long* flags = A->sy.flags + (size_t)gid * A->P.G;
   unsigned tag = A->sy.tag0;
@@ -340,7 +353,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
       st_word(&A->sy.next[gid], ((unsigned long long)tag << 32) | (unsigned)u);
     } else {
       unsigned low = ~0u;
-      if (!wait_word(&A->sy.next[gid], tag, lost ? 1 : A->sy.step_polls, low)) ish[2] = 3;
+      if (!wait_word(&A->sy.next[gid], tag, lost ? 1 : A->sy.step_polls, low)) give_up();
       u = (int)low;
     }
     ish[3] = u;
@@ -580,7 +593,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           const int nt_m = A->P.nt[m], tc_m = m == 0 ? tc[0] : m == 1 ? tc[1] : m == 2 ? tc[2] : tc[3];
           if (f ? tc_m < nt_m - 1 : tc_m > 0) {
             unsigned low;
-            if (!wait_word(&flags[tl + (f ? A->P.tgs[m] : -A->P.tgs[m])], ftag, lost ? 1 : A->sy.step_polls, low)) ish[2] = 3;
+            if (!wait_word(&flags[tl + (f ? A->P.tgs[m] : -A->P.tgs[m])], ftag, lost ? 1 : A->sy.step_polls, low)) give_up();
           }
         }
         lds_barrier();
@@ -686,7 +699,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           for (int m = 0; m < 3; ++m) t3[m] = 0;
           for (int g = j; g < A->P.G; g += 16) {
             const unsigned off = (g * lg + col) * 3 * sizeof(u4);
-            u4 w[3];
+            u4 w[3] = {u4(0), u4(0), u4(0)};
             bool ok = false;
             const int polls = lost ? 1 : A->sy.step_polls;
             for (int i = 0; i < polls && !ok; ++i) {
@@ -695,7 +708,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
               ok = w[0].y == tag && w[0].w == tag && w[1].y == tag && w[1].w == tag && w[2].y == tag && w[2].w == tag;
               asm volatile("" ::: "memory");   // read again next time
             }
-            if (!ok) ish[2] = 3;
+            if (!ok) give_up();
 #pragma unroll
             for (int m = 0; m < 3; ++m)
               t3[m] += __longlong_as_double((long long)(((unsigned long long)w[m].z << 32) | w[m].x));
@@ -710,7 +723,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
       }
       if (A->P.G > 1 && last && tid == 0) next_unit();
       lds_barrier();
-      if (A->P.G > 1) lost = lost || uniform(ish[2]) == 3;
+      if (A->P.G > 1) lost = lost || uniform(ish[2]);
       cplx<R> om[C];
 #pragma unroll
       for (int q = 0; q < C; ++q) {
@@ -740,10 +753,6 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
               if (assign) { ps[e][2 * q] = d.re; ps[e][2 * q + 1] = d.im; }
               else { ps[e][2 * q] = ps[e][2 * q] + d.re; ps[e][2 * q + 1] = ps[e][2 * q + 1] + d.im; }
             }
-          if (lost) {
-#pragma unroll
-            for (int e = 0; e < 12; ++e) ps[e] = V(__builtin_nanf(""));
-          }
         }
         if (!last && A->P.G > 1) published(tag);
         if (act) {
@@ -877,7 +886,7 @@ __global__ void __launch_bounds__(256) k_to_dom(GeomK k, DomPlan P, int L, int S
 template <typename R>
 __global__ void __launch_bounds__(256) k_from_dom(GeomK k, DomPlan P, int L, int SB, const cplx<R>* __restrict__ in,
                                                   double2* __restrict__ out, const int* __restrict__ order,
-                                                  const int* __restrict__ frozen) {
+                                                  const int* __restrict__ lost, const int* __restrict__ frozen) {
   extern __shared__ double2 gsh[];
   __shared__ DomSite ds[16];
   cplx<R>* ish = (cplx<R>*)gsh;
@@ -898,9 +907,11 @@ __global__ void __launch_bounds__(256) k_from_dom(GeomK k, DomPlan P, int L, int
     for (int e = 0; e < 12; ++e) ish[(size_t)y * row + e * L + j] = v[e];
   }
   __syncthreads();
+  const bool nan = lost && *lost;
   for (int f = tid; f < SB * row; f += nthr) {
     const int y = f / row, w = f - y * row;
-    out[(size_t)ds[y].lex * row + w] = make_double2((double)ish[f].re, (double)ish[f].im);
+    out[(size_t)ds[y].lex * row + w] = nan ? make_double2(__builtin_nan(""), __builtin_nan(""))
+                                           : make_double2((double)ish[f].re, (double)ish[f].im);
   }
 }
 
@@ -917,10 +928,12 @@ size_t lds_bytes(int prec, int C, int TS) { return (size_t)18 * (TS + 1) * vec_b
 size_t slot_bytes(const DomPlan& p, int prec) {
   return al((size_t)p.G * p.H * 6 * vec_bytes(prec, p.C));
 }
-// Words cleared before the first launch: two sets of counters, then the tagged
-// partial sums (16-byte aligned), next units and face flags of the groups.
+// Words cleared before the first launch: two sets of counters, the word of lost
+// waits, then (16-byte aligned) the tagged partial sums, next units and face
+// flags of the groups.
+constexpr int SYNC_LOST = 4, SYNC_WORDS = 8;
 size_t sync_ints(const DomPlan& p) {
-  return 4 + (size_t)p.ngroups * (8 * (size_t)p.G * 3 * p.lg + 2 * (1 + (size_t)p.G));
+  return SYNC_WORDS + (size_t)p.ngroups * (8 * (size_t)p.G * 3 * p.lg + 2 * (1 + (size_t)p.G));
 }
 // Face sizes, strides and halo places of a tile shape; false where its halo
 // or the residual's staged faces exceed the LDS rows.
@@ -1079,16 +1092,16 @@ int dom_to(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const i
   return MBBS_OK;
 }
 int dom_from(const mbbs_lattice_s* lat, int prec, int L, const DomPlan& p, const int* order, const void* in,
-             double2* out, const int* frozen, hipStream_t st) {
+             double2* out, const int* lost, const int* frozen, hipStream_t st) {
   const Geom& g = lat->g;
   const int SB = conv_sites(g.Vb, L), nb = g.V / SB, thr = (SB * L + 63) / 64 * 64;
   const size_t rows = (size_t)SB * 12 * L;
   if (prec == P64)
     hipLaunchKernelGGL(k_from_dom<double>, dim3(nb), dim3(thr), rows * 16, st, lat->gk, p, L, SB,
-                       (const cplx<double>*)in, out, order, frozen);
+                       (const cplx<double>*)in, out, order, lost, frozen);
   else
     hipLaunchKernelGGL(k_from_dom<float>, dim3(nb), dim3(thr), rows * 8, st, lat->gk, p, L, SB, (const cplx<float>*)in,
-                       out, order, frozen);
+                       out, order, lost, frozen);
   MBBS_HIP(hipGetLastError());
   return MBBS_OK;
 }
@@ -1103,9 +1116,10 @@ int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
   MBBS_TRY(dom_to(lat, b.prec, b.L, p, nullptr, in, gam, b.eta, clear, (int)nclear, frozen, st));
   if (prof) prof->end();
   DomSync sy{};
-  sy.step_polls = DOM_STEP_POLLS;
+  sy.step_polls = lat->sap_polls;
   if (p.G > 1) {
-    sy.words = (u4*)(clear + 4);
+    sy.lost = (int*)clear + SYNC_LOST;
+    sy.words = (u4*)(clear + SYNC_WORDS);
     sy.next = (unsigned long long*)(sy.words + (size_t)p.ngroups * 2 * p.G * 3 * p.lg);
     sy.flags = sy.next + p.ngroups;
     sy.slots = (char*)b.r + al(nclear * sizeof(int));
@@ -1124,7 +1138,7 @@ int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan&
     if (prof) prof->end();
   }
   if (prof) prof->begin(MBBS_K_CONVERT);
-  MBBS_TRY(dom_from(lat, b.prec, b.L, p, nullptr, b.psi, out, frozen, st));
+  MBBS_TRY(dom_from(lat, b.prec, b.L, p, nullptr, b.psi, out, sy.lost, frozen, st));
   if (prof) prof->end();
   return MBBS_OK;
 }

@@ -137,6 +137,9 @@ struct mbbs_lattice_s {
                                 // 3 on with tiles of at most half the LDS
   int tile_lg[3] = {0, 0, 0};   // columns per tiled workgroup (0: all L)
   int ncu = 0;                  // compute units of the device
+  // polls (about a microsecond each) after which a wait of one workgroup for
+  // another gives up (domsolve.hip): every wait ends
+  int sap_polls = 1 << 24;
   bool op_set[3] = {false, false, false};   // an operator setting of the precision was chosen by the caller
   int mr_once[3] = {0, 0, 0};   // MR domain solves form psi once from r_0 and the steps' A r (1) or step by step (0)
   // SSOR wavefront order inside a domain: local indices sorted by the

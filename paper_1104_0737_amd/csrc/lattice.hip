@@ -495,6 +495,13 @@ extern "C" int mbbs_lattice_tile_shape(mbbs_lattice_t lat, int L, int prec, int3
   return MBBS_OK;
 }
 
+extern "C" int mbbs_lattice_sap_polls(mbbs_lattice_t lat, int polls) {
+  MBBS_CHECK(lat != nullptr, "null lattice");
+  MBBS_CHECK(polls >= 0 && polls <= 1 << 30, "polls of a wait must be in 0..2^30");
+  lat->sap_polls = polls;
+  return MBBS_OK;
+}
+
 extern "C" int mbbs_lattice_table_size(mbbs_lattice_t lat, int which, size_t* count) {
   MBBS_CHECK(lat && count, "null argument");
   MBBS_CHECK(which >= 0 && which < MBBS_TAB_COUNT, "unknown table");

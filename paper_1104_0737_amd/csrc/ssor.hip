@@ -625,7 +625,7 @@ int ssor_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, cons
       if (prof) prof->end();
     }
   if (prof) prof->begin(MBBS_K_CONVERT);
-  MBBS_TRY(dom_from(lat, b.prec, b.L, d, lat->hp_loc, b.psi, out, frozen, st));
+  MBBS_TRY(dom_from(lat, b.prec, b.L, d, lat->hp_loc, b.psi, out, nullptr, frozen, st));
   if (prof) prof->end();
   return MBBS_OK;
 }
@@ -638,7 +638,7 @@ int ssor_blocked_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const dou
     MBBS_TRY(dom_to(lat, b.prec, b.L, d, lat->hp_loc, in, nullptr, b.r, nullptr, 0, nullptr, st));
     MBBS_TRY(ssor_planes(lat, b, p, 0, true, -1, nullptr, st));
     MBBS_TRY(ssor_planes(lat, b, p, 1, true, -1, nullptr, st));
-    return dom_from(lat, b.prec, b.L, d, lat->hp_loc, b.psi, out, nullptr, st);
+    return dom_from(lat, b.prec, b.L, d, lat->hp_loc, b.psi, out, nullptr, nullptr, st);
   }
   // r holds the input on both colours; each colour's launch reads only its
   // own domains, and psi of each colour is assigned by its launch
