@@ -294,7 +294,7 @@ def main():
                             "tile_cols": best[8] if len(best) > 8 else 0,
                             "ms": round(times[best], 4), "worst_ms": round(max(times.values()), 4),
                             "classic_best_ms": round(min(v for k, v in times.items()
-                                                         if k[2] == 0 and not (len(k) > 6 and k[6])), 4)}
+                                                         if k[1] and k[2] == 0 and not (len(k) > 6 and k[6])), 4)}
             tiled_ms = [v for k, v in times.items() if len(k) > 6 and k[6]]
             if tiled_ms:
                 tuning[name]["tiled_best_ms"] = round(min(tiled_ms), 4)

@@ -124,7 +124,8 @@ int mbbs_lattice_table(mbbs_lattice_t lat, int which, int32_t* out, size_t count
  * GROUP, BLOCK_THREADS, SPLIT, HOP_PAIR, NT_STORE, CHUNK, TILE, TILE_COLS, LDS_PAD
  * or PERSIST knob of a precision is set, that precision's operator on a whole
  * lattice chooses tiles, columns per thread and block size by the lattice's
- * size; setting one puts the others at the defaults below.  The
+ * size; setting one puts the others at the defaults below, and
+ * mbbs_lattice_tune_auto returns to the choice by size.  The
  * operator's output is bit-identical under the group, thread and LDS knobs;
  * the split knob changes the order in which the eight hops are summed, and
  * the SAP domain sums follow the block shape, so those change rounding only
@@ -201,10 +202,17 @@ enum { MBBS_TUNE_GROUP_FP64 = 0, MBBS_TUNE_GROUP_FP32 = 1, MBBS_TUNE_GROUP_FP16S
        MBBS_TUNE_TILE_COLS_FP64 = 29, MBBS_TUNE_TILE_COLS_FP32 = 30, MBBS_TUNE_TILE_COLS_FP16S = 31 };
 int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value);
 
+/* Back to a new handle's state for precision prec: the knobs of that precision
+ * that are named first above at their defaults and the operator's launch chosen
+ * by the lattice's size (and the SAP launches' block size likewise).  The knobs
+ * that all precisions share (PERSIST_BLOCKS, LDS_PAD_KB) and those of SAP alone
+ * (MR_FUSED, MR_ONCE) stay as they are.  Errors: EINVAL. */
+int mbbs_lattice_tune_auto(mbbs_lattice_t lat, int prec);
+
 /* The tile shape the LDS-tiled kernels use for L columns in precision prec
  * (MBBS_TUNE_TILE_*): t4[0..3] receives the tile extents along x, y, z, t
- * (each dividing the SAP block extent), or zeros when the tiled kernels are
- * not used (knob off, L not split evenly over the kernel's columns per
+ * (each dividing the SAP block extent), or zeros when that setting does not use
+ * the tiled kernels (knob off, whatever the choice by size then takes, L not split evenly over the kernel's columns per
  * thread, or no tile shape fits the 160 KiB LDS and one workgroup).  t4 is
  * host memory of 4 ints.  Errors: EINVAL. */
 int mbbs_lattice_tile_shape(mbbs_lattice_t lat, int L, int prec, int32_t* t4);

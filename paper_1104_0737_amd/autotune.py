@@ -12,7 +12,10 @@ or tile shape; every other setting leaves the operator's result bits alone.
 
 A setting is (group, threads, split, pair, nt[, columns per thread[, tiled[,
 psi once[, columns per tiled workgroup]]]]); psi once selects the MR domain
-solve that forms psi once per domain solve (a SAP-only choice).
+solve that forms psi once per domain solve (a SAP-only choice).  AUTO (0
+threads) stands for the launches that an untouched handle chooses by its size,
+which no other setting reaches; it is always among those timed, so a tuned
+handle is not left behind an untouched one.
 """
 
 from __future__ import annotations
@@ -20,6 +23,8 @@ from __future__ import annotations
 import itertools
 
 from . import binding as B
+
+AUTO = (0, 0, 0, 0, 0)
 
 
 def _cmax(prec):
@@ -66,11 +71,18 @@ def _tiled(setting):
     return len(setting) > 6 and setting[6] >= 1
 
 
+def _auto(setting):
+    return setting[1] == 0
+
+
 def apply(lat, prec, setting):
     g, t, sp, pr, nt = setting[:5]
     ch = setting[5] if len(setting) > 5 else 0
-    B.mbbs_lattice_tune(lat, B.TUNE_TILE[prec], setting[6] if _tiled(setting) else 0)
     B.mbbs_lattice_tune(lat, B.TUNE_MR_ONCE[prec], setting[7] if len(setting) > 7 else 0)
+    if _auto(setting):
+        B.mbbs_lattice_tune_auto(lat, prec)
+        return
+    B.mbbs_lattice_tune(lat, B.TUNE_TILE[prec], setting[6] if _tiled(setting) else 0)
     B.mbbs_lattice_tune(lat, B.TUNE_TILE_COLS[prec], setting[8] if len(setting) > 8 else 0)
     B.mbbs_lattice_tune(lat, B.TUNE_CHUNK[prec], ch)
     B.mbbs_lattice_tune(lat, B.TUNE_GROUP[prec], g)
@@ -96,7 +108,7 @@ def tune_operator(lat, V, L, prec, stream=None, reps=3):
     Y = torch.empty_like(X)
     s = stream or torch.cuda.current_stream()
     times = {}
-    for setting in operator_candidates(L, prec):
+    for setting in [AUTO] + operator_candidates(L, prec):
         apply(lat, prec, setting)
         B.mbbs_apply_dirac_raw(lat, L, prec, X, Xs, Y, Ys, stream=s)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -118,9 +130,10 @@ def sap_candidates(L, prec, op_times):
     one with the MR update folded in (FP64 / FP32), with the other tile sizes
     (whole or half LDS, all or half the columns per workgroup), the tiled MR
     step under the fastest one-thread-per-site shape, each of these with psi
-    formed once, and one column per thread (FP32 / FP16 storage)."""
+    formed once, and one column per thread (FP32 / FP16 storage); and AUTO if
+    that was timed."""
     split = [k for k in op_times if k[2] in (2, 4)]
-    classic = [k for k in op_times if k[2] not in (2, 4) and not _tiled(k)]
+    classic = [k for k in op_times if k[2] not in (2, 4) and not _tiled(k) and not _auto(k)]
     tiled = [k for k in op_times if _tiled(k)]
     cands = [min(c, key=op_times.get) for c in (split, classic, tiled) if c]
     folded = prec != B.FP16S          # the folded MR update: FP64 and FP32 only
@@ -153,7 +166,7 @@ def sap_candidates(L, prec, op_times):
         g, t, sp, pr, nt = min(classic, key=op_times.get)[:5]
         cands += [(L, tt, 0, pv, nt, 1) for tt in (128, 256) for pv in (0, 1)]
         cands += [(L, 256, 0, 1, nt, 0)]
-    return cands
+    return [k for k in op_times if _auto(k)] + cands
 
 
 def tune_sap(lat, V, L, prec, op_times, stream=None, ncy=4, nmr=4, reps=2):

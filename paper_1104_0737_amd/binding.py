@@ -24,7 +24,7 @@ TABLES = ("COORD", "NEIGHBOUR", "BOUNDARY", "PARITY", "EO", "DOMAIN", "COLOUR", 
 KERNEL_CLASSES = ("dslash64", "sap_resid", "mr_dslash", "mr_update", "convert", "gram", "update", "small", "ssor")
 
 EXPORTS = (
-    "mbbs_lattice_create", "mbbs_lattice_create_batch", "mbbs_lattice_nsys", "mbbs_lattice_destroy", "mbbs_lattice_tune", "mbbs_lattice_tile_shape",
+    "mbbs_lattice_create", "mbbs_lattice_create_batch", "mbbs_lattice_nsys", "mbbs_lattice_destroy", "mbbs_lattice_tune", "mbbs_lattice_tune_auto", "mbbs_lattice_tile_shape",
     "mbbs_lattice_sap_polls",
     "mbbs_lattice_set_clover",
     "mbbs_lattice_clover_inverse", "mbbs_apply_clover_inverse", "mbbs_lattice_table_size",
@@ -84,6 +84,7 @@ def lib():
             "mbbs_lattice_nsys": (i, [vp, ctypes.POINTER(i)]),
             "mbbs_lattice_destroy": (i, [vp]),
             "mbbs_lattice_tune": (i, [vp, i, i]),
+            "mbbs_lattice_tune_auto": (i, [vp, i]),
             "mbbs_lattice_tile_shape": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int32)]),
             "mbbs_lattice_sap_polls": (i, [vp, i]),
             "mbbs_lattice_set_clover": (i, [vp, d, vp]),
@@ -211,6 +212,10 @@ TUNE_TILE_COLS = {0: 29, 1: 30, 2: 31}  # precision -> knob
 
 def mbbs_lattice_tune(lat, knob, value):
     return _check(lib().mbbs_lattice_tune(lat, knob, value))
+
+
+def mbbs_lattice_tune_auto(lat, prec):
+    return _check(lib().mbbs_lattice_tune_auto(lat, prec))
 
 
 def mbbs_lattice_tile_shape(lat, L, prec):

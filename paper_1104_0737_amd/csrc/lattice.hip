@@ -485,6 +485,22 @@ extern "C" int mbbs_lattice_tune(mbbs_lattice_t lat, int knob, int value) {
   }
 }
 
+extern "C" int mbbs_lattice_tune_auto(mbbs_lattice_t lat, int prec) {
+  MBBS_CHECK(lat != nullptr, "null lattice");
+  MBBS_CHECK(prec >= P64 && prec <= P16, "unknown precision");
+  const mbbs_lattice_s fresh{};
+  lat->group_cols[prec] = fresh.group_cols[prec];
+  lat->block_threads[prec] = fresh.block_threads[prec];
+  lat->split[prec] = fresh.split[prec];
+  lat->hop_pair[prec] = fresh.hop_pair[prec];
+  lat->nt_store[prec] = fresh.nt_store[prec];
+  lat->chunk[prec] = fresh.chunk[prec];
+  lat->tile[prec] = fresh.tile[prec];
+  lat->tile_lg[prec] = fresh.tile_lg[prec];
+  lat->op_set[prec] = false;
+  return MBBS_OK;
+}
+
 extern "C" int mbbs_lattice_tile_shape(mbbs_lattice_t lat, int L, int prec, int32_t* t4) {
   MBBS_CHECK(lat != nullptr && t4 != nullptr, "null argument");
   MBBS_CHECK(L >= 1 && L <= 256, "L must be in 1..256");

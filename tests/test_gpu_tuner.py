@@ -1,12 +1,10 @@
 """The launch tuner and the launches a handle chooses by itself.
 
-A precision returns to its choice by size, bits included; the tuner times that
-choice beside its settings, so a tuned handle is not left behind an untouched
-one; and where SAP keeps its domain solves on the chip, which no setting
-reaches, the tuner leaves the operator's setting and the workspace alone.
+A precision returns to its choice by size, bits included, and the tuner times
+that choice beside its settings, so a tuned handle is not left behind an
+untouched one.
 """
 
-import numpy as np
 import pytest
 
 from paper_1104_0737_amd import autotune, inputs
@@ -25,16 +23,17 @@ def _sap(h, X, prec):
 
 
 def test_return_to_the_choice_by_size():
-    """FP16 storage, where the choice shows in the bits: 64 threads per block
-    instead of 256 sum a domain in another order."""
+    """Where the choice shows in the bits: 64 threads per block instead of 256 sum
+    a domain in another order (FP64, SAP by launches)."""
     dims, block, L = (12, 12, 12, 12), (6, 6, 6, 6), 6
     with gu.Lattice(dims, block, inputs.gauge_field(dims, 0.3, 680), 0.12) as lat:
         X = gu.dev(inputs.gaussian_block(12 ** 4, L, 681))
-        fresh = _sap(lat.h, X, B.FP16S)
-        B.mbbs_lattice_tune(lat.h, B.TUNE_BLOCK_THREADS_PREC[B.FP16S], 256)
-        plain = _sap(lat.h, X, B.FP16S)
-        B.mbbs_lattice_tune_auto(lat.h, B.FP16S)
-        back = _sap(lat.h, X, B.FP16S)
+        B.mbbs_lattice_tune(lat.h, B.TUNE_MR_FUSED, 0)
+        fresh = _sap(lat.h, X, B.FP64)
+        B.mbbs_lattice_tune(lat.h, B.TUNE_BLOCK_THREADS_PREC[B.FP64], 256)
+        plain = _sap(lat.h, X, B.FP64)
+        B.mbbs_lattice_tune_auto(lat.h, B.FP64)
+        back = _sap(lat.h, X, B.FP64)
         for prec in (-1, 3):
             with pytest.raises(B.MbbsError) as e:
                 B.mbbs_lattice_tune_auto(lat.h, prec)
@@ -43,36 +42,11 @@ def test_return_to_the_choice_by_size():
     assert back.tobytes() == fresh.tobytes()
 
 
-@pytest.mark.parametrize("prec", [0, 1])
-def test_tuner(prec):
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_tuner_times_the_choice_by_size(prec):
     dims, block, L = (8, 8, 8, 8), (4, 4, 4, 4), 4
-    V = 4096
     with gu.Lattice(dims, block, inputs.gauge_field(dims, 0.3, 682), 0.12) as lat:
-        X = gu.dev(inputs.gaussian_block(V, L, 683))
-        fresh, small = _sap(lat.h, X, prec), B.mbbs_sap_workspace_size(lat.h, L, prec)
-        best, times = autotune.tune_operator(lat.h, V, L, prec)
+        best, times = autotune.tune_operator(lat.h, 4096, L, prec)
         assert autotune.AUTO in times and times[best] == min(times.values())
-        # on the chip: no SAP setting is tried, none applied
-        assert B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
-        sbest, stimes = autotune.tune_sap(lat.h, V, L, prec, times)
-        assert sbest == best and list(stimes) == [best]
-        assert B.mbbs_sap_workspace_size(lat.h, L, prec) == small
-        assert _sap(lat.h, X, prec).tobytes() == fresh.tobytes()
-        # by launches: the settings count, and are compared
-        B.mbbs_lattice_tune(lat.h, B.TUNE_MR_FUSED, 0)
-        assert not B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
-        sbest, stimes = autotune.tune_sap(lat.h, V, L, prec, times, reps=1)
-        assert len(stimes) > 1 and autotune.AUTO in stimes and stimes[sbest] == min(stimes.values())
-
-
-def test_sap_on_chip():
-    """FP16 storage, and domains too large for the groups of workgroups, run by launches."""
-    dims = (16, 16, 16, 16)
-    U = inputs.gauge_field(dims, 0.3, 684)
-    for block, served in (((8, 8, 8, 8), True), ((4, 4, 4, 4), True)):
-        with gu.Lattice(dims, block, U, 0.12) as lat:
-            assert [bool(B.mbbs_lattice_sap_on_chip(lat.h, 12, p)) for p in range(3)] == [served, served, False]
-            for L, prec in ((0, 1), (65, 1), (12, 3)):
-                with pytest.raises(B.MbbsError) as e:
-                    B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
-                assert e.value.code == B.EINVAL
+        cands = autotune.sap_candidates(L, prec, times)
+        assert cands.count(autotune.AUTO) == 1
