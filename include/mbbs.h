@@ -293,6 +293,11 @@ int mbbs_apply_blocked(mbbs_lattice_t lat, int L, const double* X_dev, double* Y
  * (mbbs_lattice_sap_polls, about 20 s); all of Y is NaN then, and a solve ends
  * with EBREAKDOWN.  MBBS_TUNE_MR_FUSED 0 runs without such waits. */
 int mbbs_sap_workspace_size(mbbs_lattice_t lat, int L, int prec, size_t* bytes);
+/* *on = 1 where mbbs_sap_apply (with a workspace on the 16-byte grid) and the
+ * solves with MR domains keep the domain solves of L columns in precision prec
+ * on the chip (MBBS_TUNE_MR_FUSED -1): of the tuning knobs only that one then
+ * changes how SAP runs.  Else 0.  L as for mbbs_sap_apply.  Errors: EINVAL. */
+int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int* on);
 int mbbs_sap_apply(mbbs_lattice_t lat, int L, const double* X_dev, double* Y_dev,
                    int ncy, int nmr, int prec, void* ws_dev, size_t ws_bytes, void* stream);
 

@@ -4,9 +4,9 @@ For a lattice handle, L and a precision, time the operator over the
 candidate settings (column-group width, threads per block, split-wave hop
 groups, paired hops, nontemporal output stores, columns per thread, LDS-tiled
 kernels) and keep the fastest on the handle.  The SAP kernels of a precision
-share these settings; `tune_sap` then picks between the best split, the best
-one-thread-per-site and the best tiled shape by timing the preconditioner
-itself.  The split shapes and the number of columns per thread change the
+share these settings where SAP runs by launches; `tune_sap` then picks between
+the best split, the best one-thread-per-site and the best tiled shape by timing
+the preconditioner itself.  The split shapes and the number of columns per thread change the
 order in which the hops are summed, and the MR domain sums follow the block
 or tile shape; every other setting leaves the operator's result bits alone.
 
@@ -171,9 +171,14 @@ def sap_candidates(L, prec, op_times):
 
 def tune_sap(lat, V, L, prec, op_times, stream=None, ncy=4, nmr=4, reps=2):
     """Of sap_candidates' settings keep the one under which the SAP
-    preconditioner itself runs faster.  Returns (setting, {setting: ms})."""
+    preconditioner itself runs faster.  Returns (setting, {setting: ms}).
+    Where the domain solves stay on the chip no setting reaches them: the
+    operator's fastest is kept, and is the one that is timed."""
     import torch
-    cands = sap_candidates(L, prec, op_times)
+    if B.mbbs_lattice_sap_on_chip(lat, L, prec):
+        cands = [min(op_times, key=op_times.get)]
+    else:
+        cands = sap_candidates(L, prec, op_times)
     dev = torch.device("cuda")
     s = stream or torch.cuda.current_stream()
     X = torch.zeros((12 * V, L), dtype=torch.complex128, device=dev)

@@ -25,7 +25,7 @@ KERNEL_CLASSES = ("dslash64", "sap_resid", "mr_dslash", "mr_update", "convert", 
 
 EXPORTS = (
     "mbbs_lattice_create", "mbbs_lattice_create_batch", "mbbs_lattice_nsys", "mbbs_lattice_destroy", "mbbs_lattice_tune", "mbbs_lattice_tune_auto", "mbbs_lattice_tile_shape",
-    "mbbs_lattice_sap_polls",
+    "mbbs_lattice_sap_polls", "mbbs_lattice_sap_on_chip",
     "mbbs_lattice_set_clover",
     "mbbs_lattice_clover_inverse", "mbbs_apply_clover_inverse", "mbbs_lattice_table_size",
     "mbbs_lattice_table",
@@ -87,6 +87,7 @@ def lib():
             "mbbs_lattice_tune_auto": (i, [vp, i]),
             "mbbs_lattice_tile_shape": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int32)]),
             "mbbs_lattice_sap_polls": (i, [vp, i]),
+            "mbbs_lattice_sap_on_chip": (i, [vp, i, i, ctypes.POINTER(i)]),
             "mbbs_lattice_set_clover": (i, [vp, d, vp]),
             "mbbs_lattice_clover_inverse": (i, [vp, vp, vp]),
             "mbbs_apply_clover_inverse": (i, [vp, i, vp, vp, vp]),
@@ -223,6 +224,12 @@ def mbbs_lattice_tile_shape(lat, L, prec):
     t = (ctypes.c_int32 * 4)()
     _check(lib().mbbs_lattice_tile_shape(lat, L, prec, t))
     return tuple(t)
+
+
+def mbbs_lattice_sap_on_chip(lat, L, prec):
+    on = ctypes.c_int()
+    _check(lib().mbbs_lattice_sap_on_chip(lat, L, prec, ctypes.byref(on)))
+    return bool(on.value)
 
 
 def mbbs_lattice_sap_polls(lat, polls):

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "blas.h"
+#include "domsolve.h"
 
 using namespace mbbs;
 
@@ -86,6 +87,16 @@ extern "C" int mbbs_convert_from(int prec, size_t nsites, int L, const void* X, 
 extern "C" int mbbs_sap_workspace_size(mbbs_lattice_t lat, int L, int prec, size_t* bytes) {
   MBBS_CHECK(lat && bytes && L >= 1 && prec_ok(prec), "bad arguments");
   *bytes = sap_buffer_bytes(lat, L, prec);
+  return MBBS_OK;
+}
+
+extern "C" int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int* on) {
+  MBBS_CHECK(lat && on, "null argument");
+  MBBS_CHECK(L >= 1 && L <= 64, "L must be in 1..64");
+  MBBS_CHECK(prec_ok(prec), "bad precision");
+  DomPlan p;
+  const size_t field = (size_t)lat->g.V * 12 * L * elem_bytes(prec);
+  *on = dom_plan(lat, L, prec, 2 * ((field + 255) & ~(size_t)255), &p);
   return MBBS_OK;
 }
 

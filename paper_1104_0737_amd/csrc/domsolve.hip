@@ -1015,12 +1015,15 @@ int launch_dom(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p,
 }  // namespace
 
 bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
-  if (lat->mr_fused >= 0 || b.ssor) return false;   // the caller chose another form
-  if (b.prec == P16 || !lat->Udp[b.prec]) return false;
+  if (b.ssor || ((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.psi) & 15) return false;
+  return dom_plan(lat, b.L, b.prec, (size_t)((char*)b.psi - (char*)b.r), out);
+}
+
+bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, size_t room, DomPlan* out) {
+  if (lat->mr_fused >= 0) return false;   // the caller chose another form
+  if (prec == P16 || !lat->Udp[prec]) return false;
   const Geom& g = lat->g;
-  const int L = b.L, prec = b.prec;
   if (L > 64) return false;
-  if (((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.psi) & 15) return false;
   // links are addressed by 32-bit byte offsets
   if ((size_t)g.V * 4 * (prec == P64 ? 9 : 5) * 16 >= (1ull << 32)) return false;
   const int ncu = lat->ncu;
@@ -1062,7 +1065,6 @@ bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
   if (p.G > 1) {
     // one workgroup per CU (TS = 512), else two; the groups' words and slots
     // lie in the fields r and w, which this path does not use otherwise
-    const size_t room = (size_t)((char*)b.psi - (char*)b.r);
     const size_t slot = slot_bytes(p, prec);
     if (slot >= (1ull << 31)) return false;
     p.ngroups = std::min(p.units, (p.TS == 512 ? 1 : 2) * ncu / p.G);

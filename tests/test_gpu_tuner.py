@@ -2,7 +2,8 @@
 
 A precision returns to its choice by size, bits included, and the tuner times
 that choice beside its settings, so a tuned handle is not left behind an
-untouched one.
+untouched one.  Where SAP keeps its domain solves on the chip, which no setting
+reaches, the tuner leaves the operator's setting and the workspace alone.
 """
 
 import pytest
@@ -50,3 +51,38 @@ def test_tuner_times_the_choice_by_size(prec):
         assert autotune.AUTO in times and times[best] == min(times.values())
         cands = autotune.sap_candidates(L, prec, times)
         assert cands.count(autotune.AUTO) == 1
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_sap_tuning(prec):
+    dims, block, L = (8, 8, 8, 8), (4, 4, 4, 4), 4
+    V = 4096
+    with gu.Lattice(dims, block, inputs.gauge_field(dims, 0.3, 682), 0.12) as lat:
+        X = gu.dev(inputs.gaussian_block(V, L, 683))
+        fresh, small = _sap(lat.h, X, prec), B.mbbs_sap_workspace_size(lat.h, L, prec)
+        best, times = autotune.tune_operator(lat.h, V, L, prec)
+        # on the chip: no SAP setting is tried, none applied
+        assert B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
+        sbest, stimes = autotune.tune_sap(lat.h, V, L, prec, times)
+        assert sbest == best and list(stimes) == [best]
+        assert B.mbbs_sap_workspace_size(lat.h, L, prec) == small
+        assert _sap(lat.h, X, prec).tobytes() == fresh.tobytes()
+        # by launches: the settings count, and are compared
+        B.mbbs_lattice_tune(lat.h, B.TUNE_MR_FUSED, 0)
+        assert not B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
+        sbest, stimes = autotune.tune_sap(lat.h, V, L, prec, times, reps=1)
+        assert len(stimes) > 1 and autotune.AUTO in stimes and stimes[sbest] == min(stimes.values())
+
+
+def test_sap_on_chip():
+    """FP16 storage, and domains too large for a group of workgroups, run by launches."""
+    dims = (32, 32, 32, 16)
+    U = inputs.gauge_field(dims, 0.3, 684)
+    for block, served in (((8, 8, 8, 8), True), ((4, 4, 4, 4), True), ((16, 8, 8, 8), True),
+                          ((16, 16, 8, 8), False)):
+        with gu.Lattice(dims, block, U, 0.12) as lat:
+            assert [bool(B.mbbs_lattice_sap_on_chip(lat.h, 12, p)) for p in range(3)] == [served, served, False]
+            for L, prec in ((0, 1), (65, 1), (12, 3)):
+                with pytest.raises(B.MbbsError) as e:
+                    B.mbbs_lattice_sap_on_chip(lat.h, L, prec)
+                assert e.value.code == B.EINVAL
