@@ -62,7 +62,11 @@ enum {
  * above, caller keeps ownership; copied), hopping parameter kappa and
  * boundary phases phase[8] = (re, im) per direction, each of modulus 1.
  * The handle owns device copies of the links in FP64/FP32/FP16 in
- * lexicographic and domain-major site order.  Synchronises `stream`.
+ * lexicographic and domain-major site order (2016 bytes a site), and, where
+ * SAP or SSOR can hold the domains on the chip and the copy is below 4 GiB
+ * (SSOR: 64 GiB), plane-wise copies in FP64 and FP32 (576 and 320 bytes a site
+ * for each of the two).  Without room for the latter it does without them.
+ * Synchronises `stream`.
  * Errors: EINVAL (bad extents, blocks, phases, kappa), ENOMEM, EHIP. */
 int mbbs_lattice_create(const int dims[4], const int block[4], const double* U_dev,
                         double kappa, const double phase[8], void* stream,

@@ -962,10 +962,10 @@ bool shape_tile(const Geom& g, const int (&t)[4], int np, DomPlan* p) {
 bool pick_shape(const Geom& g, int np, int TS, DomPlan* out) {
   bool found = false;
   for (int a = 1; a <= g.b[0]; ++a)
-    for (int b = 1; b <= g.b[1]; ++b)
-      for (int c = 1; c <= g.b[2]; ++c)
-        for (int d = 1; d <= g.b[3]; ++d) {
-          if (g.b[0] % a || g.b[1] % b || g.b[2] % c || g.b[3] % d || a * b * c * d * np > TS) continue;
+    for (int b = 1; g.b[0] % a == 0 && b <= g.b[1] && a * b * np <= TS; ++b)
+      for (int c = 1; g.b[1] % b == 0 && c <= g.b[2] && a * b * c * np <= TS; ++c)
+        for (int d = 1; g.b[2] % c == 0 && d <= g.b[3] && a * b * c * d * np <= TS; ++d) {
+          if (g.b[3] % d) continue;
           DomPlan p{};
           p.TS = TS;
           const int t[4] = {a, b, c, d};
@@ -1014,6 +1014,17 @@ int launch_dom(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p,
 
 }  // namespace
 
+// Columns only make a tile larger, so one column tells whether any number of
+// them could run.  Links are addressed by 32-bit byte offsets.
+bool dom_reads_links(const mbbs_lattice_s* lat, int prec) {
+  const Geom& g = lat->g;
+  if ((size_t)g.V * 4 * (prec == P64 ? 9 : 5) * 16 >= (1ull << 32)) return false;
+  DomPlan p{};
+  for (const int TS : {256, 512})
+    if (pick_shape(g, 1, TS, &p) && 8 * p.G <= lat->ncu) return true;
+  return false;
+}
+
 bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
   if (b.ssor || ((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.psi) & 15) return false;
   return dom_plan(lat, b.L, b.prec, (size_t)((char*)b.psi - (char*)b.r), out);
@@ -1024,8 +1035,6 @@ bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, size_t room, DomPlan* 
   if (prec == P16 || !lat->Udp[prec]) return false;
   const Geom& g = lat->g;
   if (L > 64) return false;
-  // links are addressed by 32-bit byte offsets
-  if ((size_t)g.V * 4 * (prec == P64 ? 9 : 5) * 16 >= (1ull << 32)) return false;
   const int ncu = lat->ncu;
   // Two columns per thread in FP32 arithmetic (a link serves both) and the
   // largest tiles, unless a launch would then leave CUs without a workgroup.

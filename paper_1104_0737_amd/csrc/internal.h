@@ -117,9 +117,11 @@ struct mbbs_lattice_s {
   // links in the domain-plane layout per precision: 16-byte vector i of the
   // link in direction mu at local site loc of the domain at position D sits at
   // ((D 4 + mu) NL + i) Vb + loc, NL = 9 / 5 vectors per link (FP64 / FP32, the
-  // latter padded): lanes on neighbouring sites read neighbouring vectors
+  // latter padded): lanes on neighbouring sites read neighbouring vectors.
+  // Null where no kernel can read them (dom_reads_links) or memory was short
   void* Udp[2] = {nullptr, nullptr};
   // the same with the local sites in wavefront order (hp_loc) instead
+  // (ssor_reads_links)
   void* Uhp[2] = {nullptr, nullptr};
   // launch tuning (set through mbbs_lattice_tune): columns per column group
   // of the stencil kernels per precision (0: all columns in one group) and
@@ -219,6 +221,10 @@ int ssor_colour(const mbbs_lattice_s* lat, const SapBuffers& b, int colour, bool
 // SAP with SSOR domain solves through LDS, where that serves (*done), else nothing.
 int ssor_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, const double2* in, const double2* gam,
                    double2* out, const int* frozen, hipStream_t st, struct Profiler* prof, bool* done);
+// Whether SAP with MR / SSOR domains may read the plane-wise links Udp / Uhp of
+// a precision (the lattice's geometry and ncu, for SSOR also hp_max, are known).
+bool dom_reads_links(const mbbs_lattice_s* lat, int prec);
+bool ssor_reads_links(const mbbs_lattice_s* lat, int prec);
 // out = B in on every domain (both colours), FP64 lexicographic blocks.
 int ssor_blocked_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const double2* in, double2* out,
                        hipStream_t st);

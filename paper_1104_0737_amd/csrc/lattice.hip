@@ -37,7 +37,7 @@ __global__ void k_links(GeomK k, const double2* __restrict__ U, float2* __restri
 }
 
 // A plane-wise layout of the links (internal.h), from the domain-major ones;
-// order: place -> local site (null: the same).
+// order: place -> local site (null: the same); either output may be null.
 __global__ void k_link_planes(GeomK k, const int* __restrict__ order, const double2* __restrict__ U64dm, double2* __restrict__ P64p,
                               float4* __restrict__ P32p) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -49,10 +49,10 @@ __global__ void k_link_planes(GeomK k, const int* __restrict__ order, const doub
     f[9] = make_float2(0, 0);
     for (int e = 0; e < 9; ++e) {
       const double2 v = U64dm[src * 36 + mu * 9 + e];
-      P64p[((size_t)(D * 4 + mu) * 9 + e) * Vb + loc] = v;
+      if (P64p) P64p[((size_t)(D * 4 + mu) * 9 + e) * Vb + loc] = v;
       f[e] = make_float2((float)v.x, (float)v.y);
     }
-    for (int q = 0; q < 5; ++q)
+    for (int q = 0; P32p && q < 5; ++q)
       P32p[((size_t)(D * 4 + mu) * 5 + q) * Vb + loc] = make_float4(f[2 * q].x, f[2 * q].y, f[2 * q + 1].x, f[2 * q + 1].y);
   }
 }
@@ -169,23 +169,25 @@ void Profiler::flush() {
 
 using namespace mbbs;
 
+// One plane-wise copy of the links in FP64 and FP32, as far as it can be read.
+// Without room for it the kernels that read the domain-major links serve instead.
+static void link_planes(mbbs_lattice_s* lat, const int* order, bool (*read)(const mbbs_lattice_s*, int),
+                        void* (&U)[2], hipStream_t st) {
+  const size_t nl = (size_t)lat->g.V * 4 * 16;
+  for (const int p : {P64, P32})
+    if (read(lat, p) && hipMalloc(&U[p], nl * (p == P64 ? 9 : 5)) != hipSuccess) {
+      (void)hipGetLastError();
+      U[p] = nullptr;
+    }
+  if (U[P64] || U[P32])
+    hipLaunchKernelGGL(k_link_planes, dim3(ceil_div(lat->g.V, 256)), dim3(256), 0, st, lat->gk, order,
+                       (const double2*)lat->U64dm, (double2*)U[P64], (float4*)U[P32]);
+}
+
 // A lattice handle for nsys >= 1 systems of one shape: with nsys > 1 the
 // systems are stacked along t (system s owns t in [s Lt, (s + 1) Lt), its t
 // hops wrap inside that range) and every kernel of the handle treats them
 // as independent systems with hopping parameters kappa[s].
-// One plane-wise copy of the links in FP64 and FP32.  Without room for it the
-// kernels that read the domain-major links serve instead.
-static void link_planes(mbbs_lattice_s* lat, const int* order, void* (&U)[2], hipStream_t st) {
-  const size_t nl = (size_t)lat->g.V * 4 * 16;
-  if (hipMalloc(&U[P64], nl * 9) == hipSuccess && hipMalloc(&U[P32], nl * 5) == hipSuccess) {
-    hipLaunchKernelGGL(k_link_planes, dim3(ceil_div(lat->g.V, 256)), dim3(256), 0, st, lat->gk, order,
-                       (const double2*)lat->U64dm, (double2*)U[P64], (float4*)U[P32]);
-  } else {
-    (void)hipGetLastError();
-    for (void*& u : U) { (void)hipFree(u); u = nullptr; }
-  }
-}
-
 static int lattice_create(const int dims[4], const int block[4], int nsys, const double* const* U_dev,
                           const double* kappa, const double phase[8], void* stream, mbbs_lattice_t* out) {
   MBBS_CHECK(dims && block && U_dev && kappa && phase && out, "null argument");
@@ -256,7 +258,7 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
   }
   hipLaunchKernelGGL(k_links, dim3(ceil_div(V, 256)), dim3(256), 0, st, lat->gk, (const double2*)lat->U64, lat->U32,
                      lat->U16, lat->U64dm, lat->U32dm, lat->U16dm);
-  link_planes(lat, nullptr, lat->Udp, st);
+  link_planes(lat, nullptr, dom_reads_links, lat->Udp, st);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     set_error("link conversion failed");
     return fail(MBBS_EHIP);
@@ -288,7 +290,7 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
       set_error("wavefront table copy failed");
       return fail(MBBS_EHIP);
     }
-    if (g.Vb < 65535) {
+    if (ssor_reads_links(lat, P64) || ssor_reads_links(lat, P32)) {
       std::vector<int> place(g.Vb);
       for (int p = 0; p < g.Vb; ++p) place[loc[p]] = p;
       std::vector<uint2> nb(2 * (size_t)g.Vb);
@@ -321,8 +323,7 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
         set_error("wavefront table copy failed");
         return fail(MBBS_EHIP);
       }
-      // (read only where a colour's domains leave CUs idle: ssor.hip)
-      if (g.ndom / 2 / nsys <= lat->ncu / 2) link_planes(lat, lat->hp_loc, lat->Uhp, st);
+      link_planes(lat, lat->hp_loc, ssor_reads_links, lat->Uhp, st);
       if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
         set_error("link conversion failed");
         return fail(MBBS_EHIP);

@@ -532,6 +532,20 @@ __global__ void __launch_bounds__(ssor_plane_threads(PR, CL)) k_ssor_planes(Ssor
   ssor_plane_sweep<PR, CL, false, 7>(A, sh, dom, wkr, a, a, b, psi);
 }
 
+// Dynamic LDS of lg columns (two hyperplanes of 12 components, each with a cell
+// that stays zero), and what a workgroup may have.
+static size_t ssor_lds_bytes(const mbbs_lattice_s* lat, int prec, int lg) {
+  return 24 * ((size_t)lat->hp_max * lg + 1) * (prec == P64 ? 16 : 8);
+}
+constexpr size_t SSOR_LDS = 160 * 1024 - 512;
+// Links are addressed by 32-bit vector indices, places by 16 bits; for the
+// number of domains see ssor_plan.
+bool ssor_reads_links(const mbbs_lattice_s* lat, int prec) {
+  const Geom& g = lat->g;
+  return prec != P16 && g.Vb < 65535 && g.ndom / 2 / lat->nsys <= lat->ncu / 2 &&
+         ssor_lds_bytes(lat, prec, 1) <= SSOR_LDS && (size_t)g.V * 4 * (prec == P64 ? 9 : 5) < (1ull << 32);
+}
+
 // Whether and how the sweeps run through LDS.  With fewer domains of a colour
 // than CUs k_ssor leaves CUs idle; columns in workgroups of their own fill
 // them.  From half as many domains as CUs k_ssor is level or ahead (it reads a
@@ -547,10 +561,6 @@ __global__ void __launch_bounds__(ssor_plane_threads(PR, CL)) k_ssor_planes(Ssor
 static bool ssor_plan(const mbbs_lattice_s* lat, const SapBuffers& b, SsorPlan* p) {
   if (b.prec == P16 || (b.prec == P64 && lat->gk.clov) || !lat->Uhp[b.prec] || !lat->hp_nb) return false;
   if (((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.w | (uintptr_t)b.x2 | (uintptr_t)b.psi) & 15) return false;
-  // links are addressed by 32-bit vector indices
-  if ((size_t)lat->g.V * 4 * (b.prec == P64 ? 9 : 5) >= (1ull << 32)) return false;
-  const size_t elem = b.prec == P64 ? 16 : 8;
-  auto bytes = [&](int lg) { return 24 * ((size_t)lat->hp_max * lg + 1) * elem; };
   const int ncu = lat->ncu;
   // Both ways round alike, except where the compiler contracts the products of
   // boundary phases or of the clover term: there the rule looks at one system,
@@ -559,21 +569,19 @@ static bool ssor_plan(const mbbs_lattice_s* lat, const SapBuffers& b, SsorPlan* 
   for (int m = 0; m < 4; ++m) same = same && lat->g.ph[m][1] == 0.0;
   const int ndom = lat->g.ndom / 2 / (same ? 1 : lat->nsys);
   if (ndom > ncu / 2) return false;
-  const size_t lds = 160 * 1024 - 512;
   int most = ssor_plane_threads(b.prec, lat->gk.clov), lg = 1;
   for (int c = 2; c <= b.L; ++c) {
-    if (b.L % c || bytes(c) > lds) continue;
+    if (b.L % c || ssor_lds_bytes(lat, b.prec, c) > SSOR_LDS) continue;
     const int lanes = 2 * c * lat->hp_max;
     if (lanes <= 256 || (b.prec == P32 && lanes <= 1408 && ndom * (b.L / c) >= 2 * ncu)) lg = c;
   }
-  if (bytes(lg) > lds) return false;
   p->lg = lg;
   p->ncg = b.L / lg;
   // more workgroups than CUs: two at a time on each, one works while the other waits
   if (lg == 1 && ndom * p->ncg > ncu) most = std::min(most, 512);
   p->spb = std::min(lat->hp_max, most / (2 * lg));
   p->thr = (2 * p->spb * lg + 63) / 64 * 64;
-  p->lds = bytes(lg);
+  p->lds = ssor_lds_bytes(lat, b.prec, lg);
   return true;
 }
 static DomPlan ssor_storage(const mbbs_lattice_s* lat, const SsorPlan& p) {
