@@ -313,10 +313,16 @@ static int lattice_create(const int dims[4], const int block[4], int nsys, const
           else o = make_uint4(o.x | w[0], o.y | w[1], o.z | w[2], o.w | w[3]);
           nb[(size_t)f * g.Vb + p] = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
         }
+      // without room for these the SSOR kernel that does without them serves
       if (hipMalloc(&lat->hp_nb, nb.size() * sizeof(uint2)) != hipSuccess ||
           hipMalloc(&lat->hp_wrap, g.Vb * sizeof(uint4)) != hipSuccess) {
-        set_error("out of device memory for the wavefront tables");
-        return fail(MBBS_ENOMEM);
+        (void)hipGetLastError();
+        (void)hipFree(lat->hp_nb);
+        (void)hipFree(lat->hp_wrap);
+        lat->hp_nb = nullptr;
+        lat->hp_wrap = nullptr;
+        *out = lat;
+        return MBBS_OK;
       }
       if (hipMemcpy(lat->hp_nb, nb.data(), nb.size() * sizeof(uint2), hipMemcpyHostToDevice) != hipSuccess ||
           hipMemcpy(lat->hp_wrap, wrap.data(), g.Vb * sizeof(uint4), hipMemcpyHostToDevice) != hipSuccess) {
