@@ -151,8 +151,10 @@ int mbbs_lattice_table(mbbs_lattice_t lat, int which, int32_t* out, size_t count
  *      colour in one launch, one workgroup per domain (domain-wide sums inside
  *      the workgroup); 0 uses three launches per MR step spread over the whole
  *      chip; -1 (default) keeps each domain on the chip from its SAP residual to
- *      its last step, in one launch per colour and cycle (FP64 and FP32 storage;
- *      a large domain is shared by several workgroups; timed as MR_DSLASH, and
+ *      its last step, in one launch per colour and cycle (FP64 and FP32 storage,
+ *      domains that keep enough of a workgroup's lanes busy, few steps on large
+ *      domains excepted: mbbs_lattice_sap_on_chip tells where; a large domain is
+ *      shared by several workgroups; timed as MR_DSLASH, and
  *      the group, thread, split, chunk, tile, once and hop knobs do not apply),
  *      and else picks 1 when a domain holds at most 2048 (site, column) pairs
  *  MBBS_TUNE_NT_STORE_FP64/FP32/FP16S  1: the operator writes its output with
@@ -298,10 +300,11 @@ int mbbs_apply_blocked(mbbs_lattice_t lat, int L, const double* X_dev, double* Y
  * with EBREAKDOWN.  MBBS_TUNE_MR_FUSED 0 runs without such waits. */
 int mbbs_sap_workspace_size(mbbs_lattice_t lat, int L, int prec, size_t* bytes);
 /* *on = 1 where mbbs_sap_apply (with a workspace on the 16-byte grid) and the
- * solves with MR domains keep the domain solves of L columns in precision prec
- * on the chip (MBBS_TUNE_MR_FUSED -1): of the tuning knobs only that one then
- * changes how SAP runs.  Else 0.  L as for mbbs_sap_apply.  Errors: EINVAL. */
-int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int* on);
+ * solves with MR domains keep the domain solves of L columns and nmr steps in
+ * precision prec on the chip (MBBS_TUNE_MR_FUSED -1): of the tuning knobs only
+ * that one then changes how SAP runs.  Else 0.  L and nmr as for
+ * mbbs_sap_apply.  Errors: EINVAL. */
+int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int nmr, int* on);
 int mbbs_sap_apply(mbbs_lattice_t lat, int L, const double* X_dev, double* Y_dev,
                    int ncy, int nmr, int prec, void* ws_dev, size_t ws_bytes, void* stream);
 

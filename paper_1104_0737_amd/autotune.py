@@ -175,7 +175,7 @@ def tune_sap(lat, V, L, prec, op_times, stream=None, ncy=4, nmr=4, reps=2):
     Where the domain solves stay on the chip no setting reaches them: the
     operator's fastest is kept, and is the one that is timed."""
     import torch
-    if B.mbbs_lattice_sap_on_chip(lat, L, prec):
+    if B.mbbs_lattice_sap_on_chip(lat, L, prec, nmr):
         cands = [min(op_times, key=op_times.get)]
     else:
         cands = sap_candidates(L, prec, op_times)

@@ -87,7 +87,7 @@ def lib():
             "mbbs_lattice_tune_auto": (i, [vp, i]),
             "mbbs_lattice_tile_shape": (i, [vp, i, i, ctypes.POINTER(ctypes.c_int32)]),
             "mbbs_lattice_sap_polls": (i, [vp, i]),
-            "mbbs_lattice_sap_on_chip": (i, [vp, i, i, ctypes.POINTER(i)]),
+            "mbbs_lattice_sap_on_chip": (i, [vp, i, i, i, ctypes.POINTER(i)]),
             "mbbs_lattice_set_clover": (i, [vp, d, vp]),
             "mbbs_lattice_clover_inverse": (i, [vp, vp, vp]),
             "mbbs_apply_clover_inverse": (i, [vp, i, vp, vp, vp]),
@@ -226,9 +226,9 @@ def mbbs_lattice_tile_shape(lat, L, prec):
     return tuple(t)
 
 
-def mbbs_lattice_sap_on_chip(lat, L, prec):
+def mbbs_lattice_sap_on_chip(lat, L, prec, nmr=4):
     on = ctypes.c_int()
-    _check(lib().mbbs_lattice_sap_on_chip(lat, L, prec, ctypes.byref(on)))
+    _check(lib().mbbs_lattice_sap_on_chip(lat, L, prec, nmr, ctypes.byref(on)))
     return bool(on.value)
 
 

@@ -90,13 +90,14 @@ extern "C" int mbbs_sap_workspace_size(mbbs_lattice_t lat, int L, int prec, size
   return MBBS_OK;
 }
 
-extern "C" int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int* on) {
+extern "C" int mbbs_lattice_sap_on_chip(mbbs_lattice_t lat, int L, int prec, int nmr, int* on) {
   MBBS_CHECK(lat && on, "null argument");
   MBBS_CHECK(L >= 1 && L <= 64, "L must be in 1..64");
   MBBS_CHECK(prec_ok(prec), "bad precision");
+  MBBS_CHECK(nmr >= 1, "nmr must be >= 1");
   DomPlan p;
   const size_t field = (size_t)lat->g.V * 12 * L * elem_bytes(prec);
-  *on = dom_plan(lat, L, prec, 2 * ((field + 255) & ~(size_t)255), &p);
+  *on = dom_plan(lat, L, prec, nmr, 2 * ((field + 255) & ~(size_t)255), &p);
   return MBBS_OK;
 }
 

@@ -34,11 +34,11 @@ struct DomPlan {
   int ngroups;      // workgroup groups of a launch (G > 1)
 };
 
-// Whether (and how) SAP with MR domain solves runs on this path for the
-// lattice, L, precision and workspace.
-bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out);
+// Whether (and how) SAP with MR domain solves of nmr steps runs on this path for
+// the lattice, L, precision and workspace.
+bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, int nmr, DomPlan* out);
 // The same for any 16-byte aligned workspace with `room` bytes in r and w.
-bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, size_t room, DomPlan* out);
+bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, int nmr, size_t room, DomPlan* out);
 // psi = M eta on the path of `p`: in (FP64 lexicographic, times gam if given)
 // to out.  The workspace is bound as for the other SAP kernels.
 int dom_sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p, int ncy, int nmr,

@@ -975,6 +975,29 @@ bool pick_shape(const Geom& g, int np, int TS, DomPlan* out) {
   return found;
 }
 
+// Whether a plan is at least as fast as the launches it stands for.  A slot of
+// TS cells takes a step's time however few of its lanes work, so the fraction
+// of busy lanes decides; a group pays for its exchanges, which few steps do not
+// earn back; domains of a few sites have little but launches to save.  Former
+// launches' time / this form's, over 93 shapes (4096 to 10^6 sites, 1 to 13 000
+// sites a domain), 1 to 32 columns, both precisions, 1 to 4 cycles:
+//   one workgroup, at least half its lanes busy, or 0.3 and 32 sites: 2 steps
+//   and more 1.07 to 7.0, 1 step 0.86 to 3.3 (all lanes busy 0.98 to 3.3);
+//   2 to 4 workgroups as busy: 3 steps and more 1.01 to 10.6, 2 steps 0.94 to
+//   6.8 (all lanes 1.06 to 6.1), 1 step 0.72 to 4.7;
+//   more workgroups, 0.6 busy: 3 steps and more 1.13 to 13, 2 steps with all
+//   lanes 1.21 to 3.3, 1 step 0.69 to 6.2; 0.56 busy 0.93;
+//   the others at 4 steps: one workgroup 0.08 to 3.3 (1^4 domains 0.08, 2^4
+//   0.25), 2 to 4 0.68 to 4.6, more 0.10 to 4.7 (5^4 0.57).
+// (The gains among those lie where one round of workgroups holds all units; a
+// rule with rounds would run a batch's systems in another form than each alone.)
+bool dom_pays(const DomPlan& p, int Vb, int nmr) {
+  const bool all = p.T == p.TS, busy = 2 * p.T >= p.TS || (10 * p.T >= 3 * p.TS && Vb >= 32);
+  if (p.G == 1) return nmr == 1 ? all : busy;
+  if (nmr <= 2) return nmr == 2 && all;
+  return p.G <= 4 ? busy : 10 * p.T >= 6 * p.TS;
+}
+
 template <int PR, int C, int TS>
 int launch_dom_ts(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p, int colour, int mode, int nmr,
                   const DomSync& sy, const int* frozen, hipStream_t st) {
@@ -1014,23 +1037,23 @@ int launch_dom(const mbbs_lattice_s* lat, const SapBuffers& b, const DomPlan& p,
 
 }  // namespace
 
-// Columns only make a tile larger, so one column tells whether any number of
-// them could run.  Links are addressed by 32-bit byte offsets.
+// (All shapes that dom_plan considers.)  Links are addressed by 32-bit byte offsets.
 bool dom_reads_links(const mbbs_lattice_s* lat, int prec) {
   const Geom& g = lat->g;
   if ((size_t)g.V * 4 * (prec == P64 ? 9 : 5) * 16 >= (1ull << 32)) return false;
   DomPlan p{};
   for (const int TS : {256, 512})
-    if (pick_shape(g, 1, TS, &p) && 8 * p.G <= lat->ncu) return true;
+    for (int np = 1; np <= 8; np *= 2)
+      if (pick_shape(g, np, TS, &p) && 8 * p.G <= lat->ncu && dom_pays(p, g.Vb, 1 << 30)) return true;
   return false;
 }
 
-bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, DomPlan* out) {
+bool dom_plan(const mbbs_lattice_s* lat, const SapBuffers& b, int nmr, DomPlan* out) {
   if (b.ssor || ((uintptr_t)b.eta | (uintptr_t)b.r | (uintptr_t)b.psi) & 15) return false;
-  return dom_plan(lat, b.L, b.prec, (size_t)((char*)b.psi - (char*)b.r), out);
+  return dom_plan(lat, b.L, b.prec, nmr, (size_t)((char*)b.psi - (char*)b.r), out);
 }
 
-bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, size_t room, DomPlan* out) {
+bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, int nmr, size_t room, DomPlan* out) {
   if (lat->mr_fused >= 0) return false;   // the caller chose another form
   if (prec == P16 || !lat->Udp[prec]) return false;
   const Geom& g = lat->g;
@@ -1068,7 +1091,7 @@ bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, size_t room, DomPlan* 
     if (!one) consider(C, 512);
     consider(C, 256);
   }
-  if (most == 0) return false;
+  if (most == 0 || !dom_pays(p, g.Vb, nmr)) return false;
   p.units *= lat->nsys;
   p.ngroups = 1;
   if (p.G > 1) {

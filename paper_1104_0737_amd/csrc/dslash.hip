@@ -1729,7 +1729,7 @@ int sap_from(const mbbs_lattice_s* lat, const SapBuffers& b, double2* out, const
 int sap_apply(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, int nmr, const double2* in,
               const double2* gam, double2* out, const int* frozen, hipStream_t st, Profiler* prof) {
   DomPlan dp;
-  if (dom_plan(lat, b, &dp)) return dom_sap_apply(lat, b, dp, ncy, nmr, in, gam, out, frozen, st, prof);
+  if (dom_plan(lat, b, nmr, &dp)) return dom_sap_apply(lat, b, dp, ncy, nmr, in, gam, out, frozen, st, prof);
   if (b.ssor) {
     bool done = false;
     const int rc = ssor_sap_apply(lat, b, ncy, in, gam, out, frozen, st, prof, &done);

@@ -24,7 +24,8 @@ def test_sap(prec):
     with gu.Lattice(DIMS, BLOCK, inputs.gauge_field(DIMS, 0.3, 691), 0.12) as lat:
         ws = torch.zeros(B.mbbs_sap_workspace_size(lat.h, L, prec), dtype=torch.uint8, device="cuda")
         Y = torch.zeros_like(X)
-        for ncy, nmr in ((1, 1), (2, 3)):
+        for ncy, nmr in ((1, 2), (2, 3)):
+            assert B.mbbs_lattice_sap_on_chip(lat.h, L, prec, nmr)
             B.mbbs_lattice_sap_polls(lat.h, 1 << 24)
             B.mbbs_sap_apply(lat.h, L, X, Y, ncy, nmr, prec, ws)
             ref = gu.host(Y)

@@ -1,10 +1,10 @@
-"""SAP with MR domain solves on domains of one to sixteen sites, which one
-workgroup holds with room to spare, against the oracle.
+"""SAP with MR domain solves on domains of one to sixteen sites against the
+oracle, in the form that the handle chooses.
 
 The extents of 1 leave a domain few or no hops of its own; 4, 8 and 16 columns
-of such a domain share a workgroup, whose domain sums take 16 lanes per column
-whatever the number of sites.  Tolerances: the oracle's as for the other SAP
-kernels.
+of such a domain may share a workgroup, whose domain sums take 16 lanes per
+column whatever the number of sites.  Tolerances: the oracle's as for the other
+SAP kernels.
 """
 
 import numpy as np
