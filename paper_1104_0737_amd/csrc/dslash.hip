@@ -945,6 +945,17 @@ static Plan make_plan(const mbbs_lattice_s* lat, int L, int prec, int nsites, in
   return p;
 }
 
+// Share of the lanes of a block's waves that have work: S divides the domain, so
+// odd domains leave small blocks with few lanes.
+static double lanes_busy(int nchunk, int Vb, int threads) {
+  const int t = nchunk * sites_per_block(nchunk, Vb, threads);
+  return (double)t / (t + 63 & ~63);
+}
+// 64 threads a block leave about as many lanes busy as 256.
+static bool small_blocks_full(int nchunk, int Vb) {
+  return lanes_busy(nchunk, Vb, 64) >= 0.85 * lanes_busy(nchunk, Vb, 256);
+}
+
 // How the operator runs: LDS-tiled or one thread per site and C columns.
 struct OpSetting { int tile, C, threads, pair, nt; };
 
@@ -958,28 +969,55 @@ struct OpSetting { int tile, C, threads, pair, nt; };
 //    29.5 -> 25.1, 16^3 x 32 L = 12 177 -> 117, 32^3 x 64 L = 12 2857 -> 1912.  Below,
 //    staging is a latency more: FP64 8^4 L = 4 9.3 -> 16.  FP64 stores bypass the
 //    caches from 4 columns on (32^3 x 64 L = 12 4055 -> 3930; L = 1 no gain).
-//    FP16S: level with one column per thread, or behind.
+//    FP16S: level with one column per thread, or behind.  Not tiles of 8 sites
+//    (L = 64: FP64 16^4 711 -> 809, 20^4 level) nor, up to n = 400000, tiles whose
+//    last wave is nearly empty (FP32 12^4 L = 10, 80 threads: 23.1 -> 26.9), nor a
+//    few wide ones (FP32 12^4 L = 48, 1296 tiles: 106 -> 112; 20^4, 10^4: 957 -> 904).
 //  - Else one column per thread in small lattices, for more threads (FP32 8^4
 //    L = 4 14.3 -> 7.4, FP16S 14.5 -> 8.2), and from n = 200000 on with both hops of
 //    a direction in flight (FP32 24^3 x 48 L = 4 497 -> 349, L = 5 468 -> 431, FP64
-//    L = 3 581 -> 511).  Between, two columns share a link (FP32 12^4 L = 8 18.5,
+//    L = 3 581 -> 511; L = 10 where tiles do not serve: 23 -> 27, two stay).  Between, two columns share a link (FP32 12^4 L = 8 18.5,
 //    19.7 with one).  FP16S: one column also where four make whole 16-byte rows
 //    (16^3 x 32 L = 12 86 -> 82, L = 4 54 -> 38, but L = 6 71 -> 85), no pairs (L = 3
-//    50 -> 57).
+//    50 -> 57).  Domains that no tile divides (5^4, 11 x 11 x 1 x 1) make blocks of
+//    few sites, fewer still with more threads per site: there FP32 keeps two
+//    columns from L = 6 on (20^4 L = 16 285, 351 with one; L = 4 gains 1.63), FP16S
+//    four from L = 16 on (22^4 L = 24 429, 570), and pairs need more than 64 sites
+//    and busy lanes (FP64 32^4, 1^4 domains, L = 4: 6299, 7142 with pairs).
 //  - Blocks of 64 threads where 256 leave half the CUs without one (FP64 8^4 L = 1
 //    16.1 -> 8.9, L = 4 9.3 -> 7.9), or some CUs with two and some with one (FP16S
 //    clover 12^4 L = 5 18.9 -> 17.7); with more columns a block of 64 has few
-//    sites and re-reads more (8^3 x 16 L = 12 14.9 -> 17.1: 256 stays).
+//    sites and re-reads more (8^3 x 16 L = 12 14.9 -> 17.1: 256 stays), as it has
+//    where 64 threads hold few sites of an odd domain (14^4, 7^4, FP64 L = 2 25.6 ->
+//    41.1, 14 lanes of 64; 16 x 8 x 8 x 16, 8 x 4 x 4 x 8, FP32 L = 5 12.8 -> 15.0, 40
+//    lanes) unless the chip has next to nothing to do (10^4, 5^4, FP64 L = 2 1.41
+//    times as fast, 320 waves of the large blocks).
 static OpSetting op_setting(const mbbs_lattice_s* lat, int L, int prec, bool whole_op) {
   OpSetting o{-1, pick_chunk(lat, L, prec), lat->block_threads[prec], lat->hop_pair[prec], lat->nt_store[prec]};
   if (!whole_op || lat->op_set[prec]) return o;
   const size_t V = (size_t)lat->g.V / lat->nsys, n = V * L, ncu = lat->ncu;
-  o.tile = prec != P16 && (n >= 200000 || (prec == P64 && V >= 65536));
-  o.nt = o.tile && prec == P64 && L >= 4;
-  o.pair = prec != P16 && n >= 200000;
-  if (prec == P16 ? (L % 4 == 0 || n <= 256 * ncu) : (n <= 100000 || o.pair)) o.C = 1;
+  const int Vb = lat->g.Vb;
+  TileArgs T;
+  if (prec != P16 && (n >= 200000 || (prec == P64 && V >= 65536)) && tile_plan_on(lat, L, prec, &T) && T.ts >= 16) {
+    const int thr = T.ts * L / tile_cols(prec);
+    o.tile = (n >= 400000 || 10 * thr >= 7 * (thr + 63 & ~63)) && (L <= 24 || V >= 8 * ncu * T.ts);
+  }
+  o.nt = o.tile > 0 && prec == P64 && L >= 4;
+  const bool even = tile_divides(lat);
+  if (prec == P16) {
+    if ((L % 4 == 0 && (even || L <= 12)) || n <= 256 * ncu) o.C = 1;
+  } else if (n >= 200000) {
+    const bool one = o.C == 1 || L <= (even ? 8 : 4);   // one column per thread
+    o.pair = one && (even || (Vb > 64 && lanes_busy(L, Vb, 256) >= 0.6));
+    if (one) o.C = 1;
+  } else if (n <= (even ? 100000 : 50000)) {
+    o.C = 1;
+  }
   const size_t nb = ((size_t)lat->g.V * L / o.C + 255) / 256;
-  if (2 * nb <= ncu || (nb > ncu && nb <= 2 * ncu && L <= 8)) o.threads = 64;
+  const int S = sites_per_block(L / o.C, Vb);
+  const size_t waves = (size_t)lat->g.V / S * ((S * (L / o.C) + 63) / 64);
+  if ((2 * nb <= ncu || (nb > ncu && nb <= 2 * ncu && L <= 8)) && (waves < 2 * ncu || small_blocks_full(L / o.C, Vb)))
+    o.threads = 64;
   return o;
 }
 
@@ -1241,10 +1279,13 @@ constexpr int MR_OMEGA_HERE = 1024;
 
 // Threads per block of the SAP stencils: 64 instead of 256 where 256 leave CUs
 // without a block (FP16S, 12^4, L = 6, 4 cycles of 4 steps: 1179 -> 966 us; 16^3 x
-// 32, L = 12 fills them: 3803, 4025 with 64), unless the caller chose.
+// 32, L = 12 fills them: 3803, 4025 with 64) and 64 threads hold sites enough of a
+// domain (14^4, 7^4 domains, FP64 L = 2: 504, 634 with 64), unless the caller chose.
 static int sap_threads(const mbbs_lattice_s* lat, int L, int prec) {
-  const size_t n = (size_t)lat->g.Vh / lat->nsys * L / pick_chunk(lat, L, prec);
-  return !lat->op_set[prec] && (n + 255) / 256 <= (size_t)lat->ncu ? 64 : lat->block_threads[prec];
+  const int nchunk = L / pick_chunk(lat, L, prec);
+  const size_t n = (size_t)lat->g.Vh / lat->nsys * nchunk;
+  return !lat->op_set[prec] && (n + 255) / 256 <= (size_t)lat->ncu && small_blocks_full(nchunk, lat->g.Vb)
+             ? 64 : lat->block_threads[prec];
 }
 
 template <int PR, int PPSI, int PL>

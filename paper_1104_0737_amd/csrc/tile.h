@@ -29,6 +29,8 @@ inline int tile_cols(int prec) { return prec == P64 ? 1 : 2; }
 bool tile_plan(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out);
 // The same with setting 1 whatever the lattice's.
 bool tile_plan_on(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out);
+// Whether any tile shape divides the SAP block.
+bool tile_divides(const mbbs_lattice_s* lat);
 
 // out = in - kappa H in on sites [s0, s0 + n) of order `order` (whole domains;
 // LEX: the whole lattice), all hops or in-domain hops only (blocked); input

@@ -530,14 +530,13 @@ __global__ void __launch_bounds__(TILE_THREADS) k_tile(GeomK k, double kappa, in
 // scaled: FP16 storage; lg: columns per workgroup when it divides L into whole
 // column pairs of the kernel and aligned rows, else all L.  The caller checks
 // that the fields are 16-byte aligned.
+constexpr int TILE_SHAPES[][4] = {{4, 4, 4, 4}, {8, 4, 4, 2}, {4, 4, 4, 2}, {8, 4, 2, 2}, {4, 4, 2, 2}, {8, 2, 2, 2},
+                                  {4, 2, 2, 2}, {2, 2, 2, 2}, {4, 4, 2, 1}, {2, 2, 2, 1}, {2, 2, 1, 1}};
 bool pick_tile(const mbbs_lattice_s* lat, int L, size_t es, int C, bool scaled, int cap, int lg, TileArgs* out) {
-  static const int cand[][4] = {{4, 4, 4, 4}, {8, 4, 4, 2}, {4, 4, 4, 2}, {8, 4, 2, 2}, {4, 4, 2, 2},
-                                {8, 2, 2, 2}, {4, 2, 2, 2}, {2, 2, 2, 2}, {4, 4, 2, 1}, {2, 2, 2, 1},
-                                {2, 2, 1, 1}};
   const Geom& g = lat->g;
   if (L % C) return false;
   if (lg <= 0 || lg >= L || L % lg || lg % C || (lg * es) % 8 || (12 * lg * es) % 16) lg = L;
-  for (const auto& t : cand) {
+  for (const auto& t : TILE_SHAPES) {
     bool ok = true;
     for (int m = 0; m < 4; ++m) ok = ok && g.b[m] % t[m] == 0;
     if (!ok) continue;
@@ -636,6 +635,13 @@ bool tile_plan(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out) {
   if (lat->tile[prec] < 1) return false;
   return pick_tile(lat, L, elem_bytes(prec), tile_cols(prec), prec == P16, tile_cap(lat, prec), lat->tile_lg[prec],
                    out);
+}
+
+bool tile_divides(const mbbs_lattice_s* lat) {
+  const int* b = lat->g.b;
+  for (const auto& t : TILE_SHAPES)
+    if (b[0] % t[0] == 0 && b[1] % t[1] == 0 && b[2] % t[2] == 0 && b[3] % t[3] == 0) return true;
+  return false;
 }
 
 bool tile_plan_on(const mbbs_lattice_s* lat, int L, int prec, TileArgs* out) {

@@ -1,0 +1,78 @@
+"""The launches a handle chooses by size on domains that divide badly: blocks
+hold whole divisors of a domain, so an odd one leaves small blocks with few
+lanes.  The choice is compared with the plain launch (256 threads, which a handle
+runs once a knob is set): the same bits in FP64 and FP32, and a time that is not
+a quarter above it (where the choice had looked at the size alone it was 1.3 to
+1.9 times as long in each of these; the same launch twice differs by a few per
+cent)."""
+
+import numpy as np
+import pytest
+
+from paper_1104_0737_amd import inputs
+
+pytestmark = pytest.mark.gpu
+gu = pytest.importorskip("tests.gpu_util")
+torch = gu.torch
+B = gu.binding
+
+
+def _time(f, reps=40):
+    f()
+    best = 1e9
+    for _ in range(6):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(reps):
+            f()
+        e1.record()
+        e1.synchronize()
+        best = min(best, e0.elapsed_time(e1) / reps)
+    return best
+
+
+def _compare(f, plain):
+    """Times of the choice and, after plain(), of the plain launch."""
+    chosen = _time(f)
+    plain()
+    ref = _time(f)
+    return chosen, ref
+
+
+@pytest.mark.parametrize("dims,block,L,prec", [
+    ((14, 14, 14, 14), (7, 7, 7, 7), 2, 0), ((14, 14, 14, 14), (7, 7, 7, 7), 4, 1),
+    ((10, 10, 10, 10), (5, 5, 5, 5), 3, 1), ((22, 22, 22, 22), (11, 11, 1, 1), 24, 1),
+    ((26, 26, 26, 26), (13, 13, 1, 1), 24, 2)])
+def test_operator(dims, block, L, prec):
+    gu.flush(f"operator choice on odd domains {dims} {block} L={L} prec={prec}")
+    V = int(np.prod(dims))
+    U = torch.zeros((V, 4, 3, 3), dtype=torch.complex128, device="cuda")
+    U[..., range(3), range(3)] = 1
+    h = B.mbbs_lattice_create(dims, block, U, 0.12, gu.PH_AP)
+    try:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(710)
+        X = torch.randn((12 * V, L, 2), device="cuda", generator=gen)
+        X = torch.view_as_complex(X.double()) if prec == 0 else X if prec == 1 else X.half()
+        Xs = torch.ones((V, L), device="cuda") if prec == 2 else None
+        Y, Ys = torch.empty_like(X), None if Xs is None else torch.empty_like(Xs)
+        f = lambda: B.mbbs_apply_dirac_raw(h, L, prec, X, Xs, Y, Ys)
+        f()
+        bits = gu.host(Y).tobytes()
+        chosen, ref = _compare(f, lambda: B.mbbs_lattice_tune(h, B.TUNE_TILE[prec], 0))
+        assert prec == 2 or gu.host(Y).tobytes() == bits
+        assert chosen <= 1.25 * ref, (chosen, ref)
+    finally:
+        B.mbbs_lattice_destroy(h)
+
+
+def test_sap_launches():
+    dims, block, L = (22, 22, 4, 4), (11, 11, 1, 1), 24
+    V = int(np.prod(dims))
+    with gu.Lattice(dims, block, inputs.gauge_field(dims, 0.3, 711), 0.12) as lat:
+        X = gu.dev(inputs.gaussian_block(V, L, 712))
+        Y = torch.empty_like(X)
+        ws = torch.empty(B.mbbs_sap_workspace_size(lat.h, L, B.FP16S), dtype=torch.uint8, device="cuda")
+        f = lambda: B.mbbs_sap_apply(lat.h, L, X, Y, 2, 4, B.FP16S, ws)
+        chosen, ref = _compare(f, lambda: B.mbbs_lattice_tune(lat.h, B.TUNE_BLOCK_THREADS_PREC[B.FP16S], 256))
+        assert chosen <= 1.25 * ref, (chosen, ref)
