@@ -1274,8 +1274,10 @@ static bool use_mr_fused(const mbbs_lattice_s* lat, int L) {
 }
 
 // Partials (blocks x L) of a domain up to which the MR update sums them itself
-// instead of k_mr_omega before it.
-constexpr int MR_OMEGA_HERE = 1024;
+// instead of k_mr_omega before it, in blocks of at least MR_OMEGA_THREADS: more
+// and smaller blocks sum them too often (FP16S, 20^4, 5^4 domains, L = 16, 80
+// threads: 3417 us with k_mr_omega, 3604 without; 12^4, L = 6, 216: 1058, 1020).
+constexpr int MR_OMEGA_HERE = 1024, MR_OMEGA_THREADS = 128;
 
 // Threads per block of the SAP stencils: 64 instead of 256 where 256 leave CUs
 // without a block (FP16S, 12^4, L = 6, 4 cycles of 4 steps: 1179 -> 966 us; 16^3 x
@@ -1435,7 +1437,7 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
 #undef MRD
         }
         MBBS_HIP(hipGetLastError());
-        if (here) *here = nblk_dom * L <= MR_OMEGA_HERE ? nblk_dom : 0;
+        if (here) *here = nblk_dom * L <= MR_OMEGA_HERE && L * Su >= MR_OMEGA_THREADS ? nblk_dom : 0;
         if (here && *here) return MBBS_OK;
         hipLaunchKernelGGL(k_mr_omega, dim3(g.ndom / 2), dim3(256), 0, st, lat->gk, L, nblk_dom,
                            (const double*)b.partial, om, frozen);

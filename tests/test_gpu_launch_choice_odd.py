@@ -76,3 +76,21 @@ def test_sap_launches():
         f = lambda: B.mbbs_sap_apply(lat.h, L, X, Y, 2, 4, B.FP16S, ws)
         chosen, ref = _compare(f, lambda: B.mbbs_lattice_tune(lat.h, B.TUNE_BLOCK_THREADS_PREC[B.FP16S], 256))
         assert chosen <= 1.25 * ref, (chosen, ref)
+
+
+@pytest.mark.parametrize("L", [6, 16])    # the update's blocks: 150 threads, which sum omega, and 80, which do not
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_omega_by_the_size_of_the_updates_blocks(L, prec):
+    from oracle import sap
+    dims, block = (10, 10, 10, 10), (5, 5, 5, 5)
+    U = inputs.gauge_field(dims, 0.3, 713)
+    eta = inputs.gaussian_block(10 ** 4, L, 714)
+    with gu.Lattice(dims, block, U, 0.12) as lat:
+        B.mbbs_lattice_tune(lat.h, B.TUNE_MR_FUSED, 0)
+        ws = torch.empty(B.mbbs_sap_workspace_size(lat.h, L, prec), dtype=torch.uint8, device="cuda")
+        Y = torch.empty((12 * 10 ** 4, L), dtype=torch.complex128, device="cuda")
+        B.mbbs_sap_apply(lat.h, L, gu.dev(eta), Y, 2, 3, prec, ws)
+    ref = sap.sap(U, 0.12, gu.PH_AP, sap.Domains(dims, block), eta, 2, 3).reshape(12 * 10 ** 4, L)
+    tol = {0: 1e-12, 1: 3e-5, 2: 1e-2}[prec]
+    assert np.all(gu.rel_col_err(gu.host(Y), ref) <= tol)
+    assert np.all(gu.max_elem_err(gu.host(Y), ref) <= tol)
