@@ -554,6 +554,9 @@ bool ssor_reads_links(const mbbs_lattice_s* lat, int prec) {
 //   8^4 domains:  16  8.0 -> 1.4 / 12 -> 1.9,   64  6.9 -> 2.3 / 10.2 -> 3.3,
 //                128  9.4 -> 6.8 / 15.0 -> 11.2,  256  12.7 -> 13.5 / 21.6 -> 22.3
 //   6^4 domains: 128  3.0 -> 2.7 / 4.7 -> 4.0,  256  4.1 -> 4.4 / 6.5 -> 7.8
+// N_SSOR = 0 (half the sweeps, the same residual and conversions) in FP64 with many
+// columns is past the line already there: 5^4 domains, 128, L = 12 1.351 -> 1.360,
+// L = 16 1.68 -> 1.79.
 // Columns per workgroup: as many as the widest hyperplane leaves one wave per
 // SIMD (256 lanes; 8^4 sites, 4^4 domains, L = 4: 0.89 -> 0.53 ms, 0.65 with 512),
 // and in FP32, where two workgroups per CU remain, up to the thread limit.
@@ -568,7 +571,7 @@ static bool ssor_plan(const mbbs_lattice_s* lat, const SapBuffers& b, SsorPlan* 
   bool same = !lat->gk.clov;
   for (int m = 0; m < 4; ++m) same = same && lat->g.ph[m][1] == 0.0;
   const int ndom = lat->g.ndom / 2 / (same ? 1 : lat->nsys);
-  if (ndom > ncu / 2) return false;
+  if (ndom > (b.prec == P64 && b.nssor == 0 && b.L > 8 ? ncu / 4 : ncu / 2)) return false;
   int most = ssor_plane_threads(b.prec, lat->gk.clov), lg = 1;
   for (int c = 2; c <= b.L; ++c) {
     if (b.L % c || ssor_lds_bytes(lat, b.prec, c) > SSOR_LDS) continue;
