@@ -353,7 +353,8 @@ int mbbs_gram_noalloc(size_t N, int L, const double* X_dev, const double* Y_dev,
  * gamma upper triangular with positive real diagonal (the unique QR factor).
  * passes = 2 repeats the factorisation on Q (CholQR2).  Q_dev may equal P_dev.
  * gamma_dev (L x L, row-major) receives the combined factor.  Returns
- * EBREAKDOWN if P^H P is not numerically positive definite. */
+ * EBREAKDOWN if P^H P is not numerically positive definite.  The call waits for
+ * that verdict; Q and gamma are complete in the order of `stream`. */
 int mbbs_cholqr(size_t N, int L, const double* P_dev, double* Q_dev, double* gamma_dev,
                 int passes, void* ws_dev, size_t ws_bytes, void* stream);
 

@@ -241,9 +241,11 @@ extern "C" int mbbs_cholqr(size_t N, int L, const double* P, double* Q, double* 
   double2* g2 = (double2*)(q + 3 * LL);
   int* bad = (int*)(q + 5 * LL);   // per pass
   const double2* src = (const double2*)P;
-  // every launch of both passes first, those after a failed pivot without
-  // effect, then one wait for the verdict (8^4 sites, L = 4: 45.9 -> 45.3 us, of
-  // which the kernels take 21; a first call 59.6 -> 49.3)
+  // One wait for the verdict of both passes (what follows a failed pivot of the
+  // first has no effect), and not for the last product, which runs on while the
+  // caller goes on (a wait per pass, a wait behind all launches, this, in us, one
+  // pass: 8^4 sites, L = 4 45.3, 44.5, 42.9, 32^3 x 16, L = 1 41.2, 43.3, 38.4; two
+  // passes: 8^4, L = 4 86.6, 81.5, 82)
   for (int pass = 0; pass < passes; ++pass) {
     GramArgs a{};
     a.npair = 1;
@@ -254,6 +256,15 @@ extern "C" int mbbs_cholqr(size_t N, int L, const double* P, double* Q, double* 
     MBBS_TRY(launch_gram(L, N, a, o, partial, nullptr, st));
     MBBS_TRY(launch_chol_standalone(L, G, passes == 1 ? (double2*)gamma : pass == 0 ? g1 : g2, gi,
                                     pass ? bad : nullptr, bad + pass, st));
+    if (pass == passes - 1) {
+      int hbad = 0;
+      MBBS_HIP(hipMemcpyAsync(&hbad, bad + pass, sizeof(int), hipMemcpyDeviceToHost, st));
+      MBBS_HIP(hipStreamSynchronize(st));
+      if (hbad) {
+        set_error("P^H P is not numerically positive definite");
+        return MBBS_EBREAKDOWN;
+      }
+    }
     ComboArgs c{};
     c.nin = 1;
     c.mode[0] = 2;
@@ -263,13 +274,6 @@ extern "C" int mbbs_cholqr(size_t N, int L, const double* P, double* Q, double* 
     src = (const double2*)Q;
   }
   if (passes == 2) MBBS_TRY(launch_matmul_small(L, g2, g1, (double2*)gamma, bad + 1, st));
-  int hbad = 0;
-  MBBS_HIP(hipMemcpyAsync(&hbad, bad + passes - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-  MBBS_HIP(hipStreamSynchronize(st));
-  if (hbad) {
-    set_error("P^H P is not numerically positive definite");
-    return MBBS_EBREAKDOWN;
-  }
   return MBBS_OK;
 }
 
