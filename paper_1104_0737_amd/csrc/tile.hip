@@ -570,13 +570,10 @@ bool pick_tile(const mbbs_lattice_s* lat, int L, size_t es, int C, bool scaled, 
   return false;
 }
 
+// Set for each launch: a call cheap beside it, and right for every device and
+// thread, which a table of kernels already seen is not.
 void allow_tile_lds(const void* fn) {
-  static const void* seen[64];
-  static int nseen = 0;
-  for (int i = 0; i < nseen; ++i)
-    if (seen[i] == fn) return;
   (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256 * (int)sizeof(int));
-  if (nseen < 64) seen[nseen++] = fn;
 }
 
 template <int P, int C, int ORDER, int HOPS, int OP, int PPSI = P, int PL = P, int PO = P>
