@@ -986,7 +986,8 @@ struct OpSetting { int tile, C, threads, pair, nt; };
 //    and busy lanes (FP64 32^4, 1^4 domains, L = 4: 6299, 7142 with pairs).
 //  - Blocks of 64 threads where 256 leave half the CUs without one (FP64 8^4 L = 1
 //    16.1 -> 8.9, L = 4 9.3 -> 7.9), or some CUs with two and some with one (FP16S
-//    clover 12^4 L = 5 18.9 -> 17.7); with more columns a block of 64 has few
+//    clover 12^4 L = 5 18.9 -> 17.7; 31 other calls of the kind, five shapes, all
+//    precisions, 0.98 to 1.17 times as fast); with more columns a block of 64 has few
 //    sites and re-reads more (8^3 x 16 L = 12 14.9 -> 17.1: 256 stays), as it has
 //    where 64 threads hold few sites of an odd domain (14^4, 7^4, FP64 L = 2 25.6 ->
 //    41.1, 14 lanes of 64; 16 x 8 x 8 x 16, 8 x 4 x 4 x 8, FP32 L = 5 12.8 -> 15.0, 40
@@ -1282,11 +1283,12 @@ constexpr int MR_OMEGA_HERE = 1024, MR_OMEGA_THREADS = 128;
 // Threads per block of the SAP stencils: 64 instead of 256 where 256 leave CUs
 // without a block (FP16S, 12^4, L = 6, 4 cycles of 4 steps: 1179 -> 966 us; 16^3 x
 // 32, L = 12 fills them: 3803, 4025 with 64) and 64 threads hold sites enough of a
-// domain (14^4, 7^4 domains, FP64 L = 2: 504, 634 with 64), unless the caller chose.
+// domain (14^4, 7^4 domains, FP64 L = 2: 504, 634 with 64; 256 blocks, FP64 16^3 x 2,
+// 8^3 x 1 domains, L = 16: 448, 468), unless the caller chose.
 static int sap_threads(const mbbs_lattice_s* lat, int L, int prec) {
   const int nchunk = L / pick_chunk(lat, L, prec);
   const size_t n = (size_t)lat->g.Vh / lat->nsys * nchunk;
-  return !lat->op_set[prec] && (n + 255) / 256 <= (size_t)lat->ncu && small_blocks_full(nchunk, lat->g.Vb)
+  return !lat->op_set[prec] && (n + 255) / 256 < (size_t)lat->ncu && small_blocks_full(nchunk, lat->g.Vb)
              ? 64 : lat->block_threads[prec];
 }
 
