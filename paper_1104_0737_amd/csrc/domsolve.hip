@@ -308,11 +308,6 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
     // (or in this one: the waits of this group's other members end too)
     if (uniform(ish[4])) return;
   }
-  // a wait gave up
-  auto give_up = [&]() {
-    ish[2] = 1;
-    __hip_atomic_store(A->sy.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
   const __amdgpu_buffer_rsrc_t rs = dev_rsrc(A->sy.slots + (size_t)gid * A->sy.slot_bytes, A->sy.slot_bytes);
   unsigned long long* flags = A->sy.flags + (size_t)gid * A->P.G;
   unsigned tag = A->sy.tag0;
@@ -353,7 +348,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
       st_word(&A->sy.next[gid], ((unsigned long long)tag << 32) | (unsigned)u);
     } else {
       unsigned low = ~0u;
-      if (!wait_word(&A->sy.next[gid], tag, lost ? 1 : A->sy.step_polls, low)) give_up();
+      if (!wait_word(&A->sy.next[gid], tag, lost ? 1 : A->sy.step_polls, low)) ish[2] = 1;
       u = (int)low;
     }
     ish[3] = u;
@@ -593,7 +588,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           const int nt_m = A->P.nt[m], tc_m = m == 0 ? tc[0] : m == 1 ? tc[1] : m == 2 ? tc[2] : tc[3];
           if (f ? tc_m < nt_m - 1 : tc_m > 0) {
             unsigned low;
-            if (!wait_word(&flags[tl + (f ? A->P.tgs[m] : -A->P.tgs[m])], ftag, lost ? 1 : A->sy.step_polls, low)) give_up();
+            if (!wait_word(&flags[tl + (f ? A->P.tgs[m] : -A->P.tgs[m])], ftag, lost ? 1 : A->sy.step_polls, low)) ish[2] = 1;
           }
         }
         lds_barrier();
@@ -699,16 +694,16 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
           for (int m = 0; m < 3; ++m) t3[m] = 0;
           for (int g = j; g < A->P.G; g += 16) {
             const unsigned off = (g * lg + col) * 3 * sizeof(u4);
-            u4 w[3] = {u4(0), u4(0), u4(0)};
-            bool ok = false;
-            const int polls = lost ? 1 : A->sy.step_polls;
-            for (int i = 0; i < polls && !ok; ++i) {
+            u4 w[3];
+            bool ok;
+            int polls = lost ? 1 : A->sy.step_polls;
+            do {
 #pragma unroll
               for (int m = 0; m < 3; ++m) w[m] = ld_dev<u4>(wrs, off + m * sizeof(u4));
               ok = w[0].y == tag && w[0].w == tag && w[1].y == tag && w[1].w == tag && w[2].y == tag && w[2].w == tag;
               asm volatile("" ::: "memory");   // read again next time
-            }
-            if (!ok) give_up();
+            } while (!ok && --polls > 0);
+            if (!ok) ish[2] = 1;
 #pragma unroll
             for (int m = 0; m < 3; ++m)
               t3[m] += __longlong_as_double((long long)(((unsigned long long)w[m].z << 32) | w[m].x));
@@ -753,6 +748,12 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
               if (assign) { ps[e][2 * q] = d.re; ps[e][2 * q + 1] = d.im; }
               else { ps[e][2 * q] = ps[e][2 * q] + d.re; ps[e][2 * q + 1] = ps[e][2 * q + 1] + d.im; }
             }
+          // (the result becomes NaN in any case; without this branch the compiler
+          // orders the update worse: FP32 32^3 x 64 40.4 -> 41.5 ms)
+          if (lost) {
+#pragma unroll
+            for (int e = 0; e < 12; ++e) ps[e] = V(__builtin_nanf(""));
+          }
         }
         if (!last && A->P.G > 1) published(tag);
         if (act) {
@@ -767,6 +768,7 @@ __global__ void __launch_bounds__(TS, 2) k_dom(DomArgs) {
     if (lost) unit = -1;
     lds_barrier();
   }
+  if (A->P.G > 1 && tid == 0 && ish[2]) __hip_atomic_store(A->sy.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------------------- conversions
@@ -1057,7 +1059,7 @@ bool dom_plan(const mbbs_lattice_s* lat, int L, int prec, int nmr, size_t room, 
   if (lat->mr_fused >= 0) return false;   // the caller chose another form
   if (prec == P16 || !lat->Udp[prec]) return false;
   const Geom& g = lat->g;
-  if (L > 64) return false;
+  if (L > 64 || (nmr == 1 && g.Vb > 256)) return false;   // (the latter: no search for what dom_pays refuses)
   const int ncu = lat->ncu;
   // Two columns per thread in FP32 arithmetic (a link serves both) and the
   // largest tiles, unless a launch would then leave CUs without a workgroup.
