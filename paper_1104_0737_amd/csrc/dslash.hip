@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(256) k_mr_omega(GeomK k, int L, int nblk, cons
 // MR step, part 2: psi += omega r ; r -= omega w  (per domain and column).
 // SUMS: omega is given as the domain's nblk block partials, which every block
 // (its sites lie in one domain) sums for itself: a launch less where they are
-// few (MR_OMEGA_HERE).
+// few (omega_in_update).
 template <int PR, int PPSI, bool SUMS = false>
 __global__ void __launch_bounds__(256) k_mr_update(GeomK k, int L, int s0, int n,
                                                    typename Store<PR>::Elem* __restrict__ r,
@@ -920,10 +920,9 @@ GeomK make_geomk(const Geom& g, int nsys) {
 // Sites per block so that blockDim = (L/C, S) has about `target` threads and S
 // divides `vdiv` (so blocks never straddle SAP domains when vdiv = Vb).
 static int sites_per_block(int nchunk, int vdiv, int target = 256) {
-  int best = 1;
-  for (int s = 1; s * nchunk <= target; ++s)
-    if (vdiv % s == 0) best = s;
-  return best;
+  for (int s = std::min(target / nchunk, vdiv); s > 1; --s)
+    if (vdiv % s == 0) return s;
+  return 1;
 }
 
 // Launch plan of a stencil kernel over `nsites` sites (a multiple of the
@@ -951,9 +950,14 @@ static double lanes_busy(int nchunk, int Vb, int threads) {
   const int t = nchunk * sites_per_block(nchunk, Vb, threads);
   return (double)t / (t + 63 & ~63);
 }
-// 64 threads a block leave about as many lanes busy as 256.
-static bool small_blocks_full(int nchunk, int Vb) {
-  return lanes_busy(nchunk, Vb, 64) >= 0.85 * lanes_busy(nchunk, Vb, 256);
+// Blocks of 64 threads may stand in for 256: about as many lanes stay busy, or
+// half of them do and blocks of 256 are next to nothing for the chip (fewer than
+// two waves a CU).
+static bool small_blocks(const mbbs_lattice_s* lat, size_t nsites, int nchunk) {
+  const int Vb = lat->g.Vb, S = sites_per_block(nchunk, Vb);
+  const double busy = lanes_busy(nchunk, Vb, 64);
+  return (busy >= 0.5 && nsites / S * ((S * nchunk + 63) / 64) < 2 * (size_t)lat->ncu) ||
+         busy >= 0.85 * lanes_busy(nchunk, Vb, 256);
 }
 
 // How the operator runs: LDS-tiled or one thread per site and C columns.
@@ -1015,10 +1019,7 @@ static OpSetting op_setting(const mbbs_lattice_s* lat, int L, int prec, bool who
     o.C = 1;
   }
   const size_t nb = ((size_t)lat->g.V * L / o.C + 255) / 256;
-  const int S = sites_per_block(L / o.C, Vb);
-  const size_t waves = (size_t)lat->g.V / S * ((S * (L / o.C) + 63) / 64);
-  if ((2 * nb <= ncu || (nb > ncu && nb <= 2 * ncu && L <= 8)) && (waves < 2 * ncu || small_blocks_full(L / o.C, Vb)))
-    o.threads = 64;
+  if ((2 * nb <= ncu || (nb > ncu && nb <= 2 * ncu && L <= 8)) && small_blocks(lat, lat->g.V, L / o.C)) o.threads = 64;
   return o;
 }
 
@@ -1274,21 +1275,26 @@ static bool use_mr_fused(const mbbs_lattice_s* lat, int L) {
   return (size_t)lat->g.Vb * L <= 2048;
 }
 
-// Partials (blocks x L) of a domain up to which the MR update sums them itself
-// instead of k_mr_omega before it, in blocks of at least MR_OMEGA_THREADS: more
-// and smaller blocks sum them too often (FP16S, 20^4, 5^4 domains, L = 16, 80
-// threads: 3417 us with k_mr_omega, 3604 without; 12^4, L = 6, 216: 1058, 1020).
-constexpr int MR_OMEGA_HERE = 1024, MR_OMEGA_THREADS = 128;
+// Whether the MR update sums a domain's `sums` partials (blocks x L) itself
+// instead of k_mr_omega before it: a launch less (3 % in the median of 450 cases),
+// but each of its `blocks` of `threads` sums them, so not where they are small
+// (FP16S, 20^4, 5^4 domains, L = 16, 80 threads: 3417 us with k_mr_omega, 3604
+// without) or where many blocks sum much (FP16S, 24^4, 12^3 x 6 domains, L = 6, 4608
+// blocks, 768 partials: 3209, 3431; up to 4 blocks a CU 0.99 to 1.09 times as fast).
+static bool omega_in_update(const mbbs_lattice_s* lat, int sums, int blocks, int threads) {
+  return threads >= 128 && sums <= (blocks <= 4 * lat->ncu ? 1024 : 512);
+}
 
 // Threads per block of the SAP stencils: 64 instead of 256 where 256 leave CUs
 // without a block (FP16S, 12^4, L = 6, 4 cycles of 4 steps: 1179 -> 966 us; 16^3 x
 // 32, L = 12 fills them: 3803, 4025 with 64) and 64 threads hold sites enough of a
-// domain (14^4, 7^4 domains, FP64 L = 2: 504, 634 with 64; 256 blocks, FP64 16^3 x 2,
-// 8^3 x 1 domains, L = 16: 448, 468), unless the caller chose.
+// domain (14^4, 7^4 domains, FP64 L = 2: 504, 634 with 64), unless the caller chose.
+// At 256 blocks for 256 CUs FP16S gains (16^4, L = 4: 1412 -> 1247), FP64 does not
+// (16^3 x 2, 8^3 x 1 domains, L = 16: 448, 468).
 static int sap_threads(const mbbs_lattice_s* lat, int L, int prec) {
   const int nchunk = L / pick_chunk(lat, L, prec);
-  const size_t n = (size_t)lat->g.Vh / lat->nsys * nchunk;
-  return !lat->op_set[prec] && (n + 255) / 256 < (size_t)lat->ncu && small_blocks_full(nchunk, lat->g.Vb)
+  const size_t nsites = (size_t)lat->g.Vh / lat->nsys, nb = (nsites * nchunk + 255) / 256;
+  return !lat->op_set[prec] && nb < (size_t)lat->ncu + (prec == P16) && small_blocks(lat, nsites, nchunk)
              ? 64 : lat->block_threads[prec];
 }
 
@@ -1439,7 +1445,7 @@ static int sap_cycles(const mbbs_lattice_s* lat, const SapBuffers& b, int ncy, i
 #undef MRD
         }
         MBBS_HIP(hipGetLastError());
-        if (here) *here = nblk_dom * L <= MR_OMEGA_HERE && L * Su >= MR_OMEGA_THREADS ? nblk_dom : 0;
+        if (here) *here = omega_in_update(lat, nblk_dom * L, ceil_div(n, Su), L * Su) ? nblk_dom : 0;
         if (here && *here) return MBBS_OK;
         hipLaunchKernelGGL(k_mr_omega, dim3(g.ndom / 2), dim3(256), 0, st, lat->gk, L, nblk_dom,
                            (const double*)b.partial, om, frozen);
