@@ -7,7 +7,7 @@
 // last update: eta passes once, psi once per step (through L2), and the FP32
 // vector units and the latencies of the exchange, not HBM, bound the launch.
 // Measured, SAP with 4 cycles of 4 steps, 8^4 domains, 12 columns: FP32 on
-// 32^3 x 64 sites 79.7 -> 40.6 ms, FP64 on 16^3 x 32 10.4 -> 5.98 ms; 4^4
+// 32^3 x 64 sites 79.7 -> 40.4 ms, FP64 on 16^3 x 32 10.4 -> 5.82 ms; 4^4
 // domains, 8^4 sites, 4 columns (2 cycles): FP32 0.52 -> 0.17 ms.
 //
 // A domain that fits one workgroup (256 threads, one site and C columns each)
