@@ -4,8 +4,10 @@
 // As launches of their own, the parts of an MR step stream about 27 field
 // passes per domain solve through HBM.  Here a unit (domain x column group)
 // keeps its residual r in LDS and A r in registers from the first hop to the
-// last update: eta passes once, psi once per step (through L2), and the FP32
-// vector units and the latencies of the exchange, not HBM, bound the launch.
+// last update: eta passes once, psi once per step.  Counted at 32^3 x 64 in FP32:
+// vector instructions fill about half of a launch's cycles; with the exchange,
+// past the L2s, memory moves 16.5 to 26.5 GB (3.5 to 5.6 TB/s) where 4.3 GB are
+// compulsory.  The two, and the waits of a step in series, share the bound.
 // Measured, SAP with 4 cycles of 4 steps, 8^4 domains, 12 columns: FP32 on
 // 32^3 x 64 sites 79.7 -> 40.4 ms, FP64 on 16^3 x 32 10.4 -> 5.82 ms; 4^4
 // domains, 8^4 sites, 4 columns (2 cycles): FP32 0.52 -> 0.17 ms.
